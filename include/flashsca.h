@@ -158,6 +158,40 @@ int flashsca_backward(const flashsca_value *value, const float *lidar2img,
                       float *grad_logits, void *stream);
 
 /*
+ * The same backward in binned form, on a caller workspace.  The points are
+ * grouped by the pixels they touch and every element of the value gradient is
+ * summed and written once, without float atomics (a call whose points exceed
+ * the workspace's records, more than two per point, and a group of queries
+ * whose points spread over very many pixel bins are scattered as in
+ * flashsca_backward, decided on the device).
+ *
+ *   grad_value         as in flashsca_backward, but in `grad_value_dtype`:
+ *                      FLASHBEV_F32, or the value's dtype (the float32 sum
+ *                      rounded once to nearest even), aligned to it.
+ *   workspace          device, at least flashsca_backward_workspace_size
+ *                      bytes, 256-byte aligned, disjoint from every other
+ *                      buffer; its contents need not be kept between calls.
+ *                      Calls that may overlap need a workspace each.
+ *
+ * FLASHBEV_ERR_UNSUPPORTED where the binned form does not serve the shape
+ * (head rows other than 8, 16, 24, 32, 48 or 64 channels, an empty output, no
+ * cameras, or more than 2^28 points); FLASHBEV_ERR_SCRATCH for a workspace
+ * that is too small.  The scatter form is the faster one for few points.
+ */
+int flashsca_backward_ws(const flashsca_value *value, const float *lidar2img,
+                         const flashbev_bev_grid_spec *spec, const flashbev_z_bins *anchors,
+                         int32_t P, const float *offsets, const float *logits,
+                         const float *grad_out, void *grad_value, int32_t grad_value_dtype,
+                         float *grad_offsets, float *grad_logits, void *workspace,
+                         uint64_t workspace_bytes, void *stream);
+
+/* Workspace bytes of flashsca_backward_ws for these arguments; no HIP call. */
+int flashsca_backward_workspace_size(const flashsca_value *value,
+                                     const flashbev_bev_grid_spec *spec,
+                                     const flashbev_z_bins *anchors, int32_t P,
+                                     uint64_t *bytes);
+
+/*
  * Launch geometry of flashsca_forward for these arguments: workgroups,
  * threads per workgroup, dynamic LDS bytes per workgroup, lanes per
  * (query, head) and bytes each lane loads per tap.  Same checks as the

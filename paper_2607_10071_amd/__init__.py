@@ -148,6 +148,15 @@ def _lib():
         L.flashsca_backward.argtypes = [P(ScaValue), ctypes.c_void_p, P(GridSpec), P(ZBins),
                                         ctypes.c_int32] + [ctypes.c_void_p] * 7
         L.flashsca_backward.restype = ctypes.c_int
+        L.flashsca_backward_workspace_size.argtypes = [P(ScaValue), P(GridSpec), P(ZBins),
+                                                       ctypes.c_int32, P(ctypes.c_uint64)]
+        L.flashsca_backward_workspace_size.restype = ctypes.c_int
+        L.flashsca_backward_ws.argtypes = [P(ScaValue), ctypes.c_void_p, P(GridSpec), P(ZBins),
+                                           ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p,
+                                           ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
+                                           ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
+                                           ctypes.c_uint64, ctypes.c_void_p]
+        L.flashsca_backward_ws.restype = ctypes.c_int
         L.flashsca_backward_launch_info.argtypes = L.flashsca_launch_info.argtypes
         L.flashsca_backward_launch_info.restype = ctypes.c_int
         _LIB = L
@@ -770,48 +779,127 @@ def _sca_bwd_outputs(value, Q, heads, L, P, grad_value, grad_offsets, grad_logit
     return out
 
 
+SCA_BACKWARD_METHODS = ("auto", "binned", "scatter")
+# Points (B X Y heads L P) from which "auto" takes the binned form: its six
+# launches cost more than the scatter form's atomics below (MI355X, scatter /
+# binned us: 160,000 points 61 / 68; 320,000 124 / 108; 2,560,000 563 / 416;
+# 10,240,000 1450 / 1060).
+SCA_BINNED_MIN_POINTS = 1 << 18
+
+
+def _sca_workspace_bytes(v, g, zb, P: int, method: str, points: int, grad_value) -> int:
+    """Workspace bytes of the binned backward, or -1 where the scatter form
+    is taken: "auto" takes it for few points, for calls that want no value
+    gradient (the two are one kernel there), and for shapes the binned form
+    does not serve."""
+    if method not in SCA_BACKWARD_METHODS:
+        raise ValueError(f"method must be one of {SCA_BACKWARD_METHODS}")
+    if method == "scatter" or (method == "auto" and (grad_value is None
+                                                     or points < SCA_BINNED_MIN_POINTS)):
+        return -1
+    out = ctypes.c_uint64()
+    rc = _lib().flashsca_backward_workspace_size(ctypes.byref(v), ctypes.byref(g),
+                                                 ctypes.byref(zb), P, ctypes.byref(out))
+    if rc == STATUS["OK"]:
+        return int(out.value)
+    if method == "binned" and rc != STATUS["ERR_UNSUPPORTED"]:
+        raise FlashBevError(rc, "flashsca_backward_workspace_size")
+    return -1   # the scatter form's own checks report what is wrong
+
+
+def _sca_workspace(need: int, device, s: int):
+    """The binned backward's workspace, held for the stream that uses it; None
+    where the device has no room for it (the scatter form needs none)."""
+    import torch
+
+    try:
+        ws = torch.empty(need, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+    if s != torch.cuda.current_stream(device).cuda_stream:
+        ws.record_stream(torch.cuda.ExternalStream(s, device=device))
+    return ws
+
+
 def sca_backward(value, lidar2img, anchors, grid: BevGrid, img_hw, levels, heads: int, offsets,
                  logits, grad_out, grad_value=None, grad_offsets=None, grad_logits=None,
-                 want=("value", "offsets", "logits"), reduce: str = "mean", stream=None):
+                 want=("value", "offsets", "logits"), reduce: str = "mean", stream=None,
+                 method: str = "auto"):
     """FlashSCA backward on the GPU: gradients with respect to the value maps,
     the offsets and the logits for ``grad_out`` [B, X*Y, C] float32.
+
+    method   "binned" (flashsca_backward_ws: the points are grouped by pixel
+             and the value gradient written once; it needs a device
+             workspace, allocated here), "scatter" (flashsca_backward: float
+             atomics, no workspace) or "auto" (binned from
+             SCA_BINNED_MIN_POINTS points on).  The scatter form serves the
+             shapes the binned form does not.
 
     Returns a dict with the float32 tensors ``value`` [B, N, S, C],
     ``offsets`` [B, X*Y, heads, L, P, 2] and ``logits`` [B, X*Y, heads, L, P]
     (None for gradients not in ``want`` and not passed in).  Asynchronous.
     """
+    return _sca_backward(value, lidar2img, anchors, grid, img_hw, levels, heads, offsets, logits,
+                         grad_out, grad_value, grad_offsets, grad_logits, want, reduce, stream,
+                         method, None)
+
+
+def _sca_backward(value, lidar2img, anchors, grid, img_hw, levels, heads, offsets, logits,
+                  grad_out, grad_value, grad_offsets, grad_logits, want, reduce, stream, method,
+                  value_dtype):
+    """sca_backward; ``value_dtype`` (a torch dtype) asks for the value gradient
+    in the value maps' type, rounded once."""
     import torch
 
     B, N, S, C, Q, P = _sca_check(value, lidar2img, offsets, logits, levels, heads, grid)
     if not grad_out.is_cuda or grad_out.dtype != torch.float32 or not grad_out.is_contiguous() \
             or tuple(grad_out.shape) != (B, Q, C):
         raise ValueError(f"grad_out must be a contiguous float32 device tensor [{B}, {Q}, {C}]")
-    outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,
-                            grad_logits, want)
     z = _z_array(anchors)
     v, g, zb = _sca_structs(value.shape, _dtype_code(value), value.data_ptr(), heads, levels,
                             img_hw, grid, z, reduce)
-    dev = _one_device(value, lidar2img, offsets, logits, grad_out, *outs.values())
+    dev = _one_device(value, lidar2img, offsets, logits, grad_out,
+                      *(t for t in (grad_value, grad_offsets, grad_logits) if t is not None))
     s = _stream_handle(stream, dev)
+    wants_value = grad_value is not None or "value" in want
+    need = _sca_workspace_bytes(v, g, zb, P, method, logits.numel(), wants_value or None)
+    ws = _sca_workspace(need, dev, s) if need >= 0 else None
+    convert = value_dtype is not None and value_dtype != torch.float32 and wants_value
+    if convert and ws is not None:
+        grad_value = torch.empty((B, N, S, C), dtype=value_dtype, device=dev)
+        outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, None, grad_offsets, grad_logits,
+                                tuple(k for k in want if k != "value"))
+        outs["value"] = grad_value
+    else:
+        outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,
+                                grad_logits, want)
     ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else 0)
+    ins = (ctypes.byref(v), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
+           ctypes.byref(zb), P, ctypes.c_void_p(offsets.data_ptr()),
+           ctypes.c_void_p(logits.data_ptr()), ctypes.c_void_p(grad_out.data_ptr()),
+           ptr(outs["value"]))
+    rest = (ptr(outs["offsets"]), ptr(outs["logits"]))
     with _on_device(dev):
-        rc = _lib().flashsca_backward(ctypes.byref(v), ctypes.c_void_p(lidar2img.data_ptr()),
-                                      ctypes.byref(g), ctypes.byref(zb), P,
-                                      ctypes.c_void_p(offsets.data_ptr()),
-                                      ctypes.c_void_p(logits.data_ptr()),
-                                      ctypes.c_void_p(grad_out.data_ptr()), ptr(outs["value"]),
-                                      ptr(outs["offsets"]), ptr(outs["logits"]),
-                                      ctypes.c_void_p(s))
+        if ws is not None:
+            gv = outs["value"]
+            code = _dtype_code(gv) if gv is not None else DTYPE_CODES["f32"]
+            rc = _lib().flashsca_backward_ws(*ins, code, *rest, ctypes.c_void_p(ws.data_ptr()),
+                                             ctypes.c_uint64(need), ctypes.c_void_p(s))
+        else:
+            rc = _lib().flashsca_backward(*ins, *rest, ctypes.c_void_p(s))
     if rc != 0:
         raise FlashBevError(rc, "flashsca_backward")
+    if convert and ws is None:
+        outs["value"] = outs["value"].to(value_dtype)
     return outs
 
 
 def prepare_sca_backward(value, lidar2img, anchors, grid: BevGrid, img_hw, levels, heads: int,
                          offsets, logits, grad_out, grad_value, grad_offsets, grad_logits,
-                         reduce: str = "mean", stream=None) -> _Prepared:
+                         reduce: str = "mean", stream=None, method: str = "auto") -> _Prepared:
     """``sca_backward`` with every argument fixed (outputs given; any may be
-    None): a callable that enqueues the same call again."""
+    None): a callable that enqueues the same call again.  The binned form's
+    workspace is allocated once, here."""
     B, N, S, C, Q, P = _sca_check(value, lidar2img, offsets, logits, levels, heads, grid)
     outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,
                             grad_logits, ())
@@ -821,12 +909,19 @@ def prepare_sca_backward(value, lidar2img, anchors, grid: BevGrid, img_hw, level
     dev = _one_device(value, lidar2img, offsets, logits, grad_out, *outs.values())
     s = _stream_handle(stream, dev)
     ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else 0)
-    args = (ctypes.byref(v), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
-            ctypes.byref(zb), ctypes.c_int32(P), ctypes.c_void_p(offsets.data_ptr()),
-            ctypes.c_void_p(logits.data_ptr()), ctypes.c_void_p(grad_out.data_ptr()),
-            ptr(outs["value"]), ptr(outs["offsets"]), ptr(outs["logits"]), ctypes.c_void_p(s))
-    return _Prepared(_lib().flashsca_backward, args,
-                     (value, lidar2img, offsets, logits, grad_out, outs, z, v, g, zb),
+    need = _sca_workspace_bytes(v, g, zb, P, method, logits.numel(), outs["value"])
+    ws = _sca_workspace(need, dev, s) if need >= 0 else None
+    ins = (ctypes.byref(v), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
+           ctypes.byref(zb), ctypes.c_int32(P), ctypes.c_void_p(offsets.data_ptr()),
+           ctypes.c_void_p(logits.data_ptr()), ctypes.c_void_p(grad_out.data_ptr()),
+           ptr(outs["value"]))
+    rest = (ptr(outs["offsets"]), ptr(outs["logits"]))
+    keep = (value, lidar2img, offsets, logits, grad_out, outs, ws, z, v, g, zb)
+    if ws is not None:
+        args = (*ins, ctypes.c_int32(DTYPE_CODES["f32"]), *rest, ctypes.c_void_p(ws.data_ptr()),
+                ctypes.c_uint64(need), ctypes.c_void_p(s))
+        return _Prepared(_lib().flashsca_backward_ws, args, keep, "flashsca_backward_ws", dev)
+    return _Prepared(_lib().flashsca_backward, (*ins, *rest, ctypes.c_void_p(s)), keep,
                      "flashsca_backward", dev)
 
 
@@ -880,12 +975,10 @@ def _autograd_functions():
                          if ctx.needs_input_grad[i])
             if not want:
                 return (None,) * 10
-            r = sca_backward(value, l2i, anchors, grid, img_hw, levels, heads, off, lg,
-                             grad_out.float().contiguous(), want=want, reduce=reduce)
-            gv = r["value"]
-            if gv is not None and gv.dtype != value.dtype:
-                gv = gv.to(value.dtype)
-            return gv, None, r["offsets"], r["logits"], None, None, None, None, None, None
+            r = _sca_backward(value, l2i, anchors, grid, img_hw, levels, heads, off, lg,
+                              grad_out.float().contiguous(), None, None, None, want, reduce,
+                              None, "auto", value.dtype)
+            return r["value"], None, r["offsets"], r["logits"], None, None, None, None, None, None
 
     _AUTOGRAD["sample_vt"] = _SampleVT
     _AUTOGRAD["sca"] = _SCA

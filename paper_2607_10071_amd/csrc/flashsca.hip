@@ -37,10 +37,11 @@
 //         value-gradient row), sums each key's members and scatters one
 //         float atomic add per distinct row and channel.
 //   * Forward: each output element is written once, no atomics on global
-//     memory, no workspace, one launch.  Backward: a fill kernel zeroes the
-//     value gradient, then one launch; every offset and logit gradient is
-//     written (the logit gradient holds d a_j until the slot's softmax
-//     backward finishes it).
+//     memory, no workspace, one launch.  Backward, scatter form (above; no
+//     workspace): a fill kernel zeroes the value gradient, then one launch;
+//     every offset and logit gradient is written (the logit gradient holds
+//     d a_j until the slot's softmax backward finishes it).  Backward, binned
+//     form (a caller workspace): see "Binned backward" below.
 // Coordinates follow the float32 recipe of the conventions in flashsca.h, so
 // mask and floor decisions match the CPU oracle bit for bit: the file is
 // compiled with -ffp-contract=off and uses IEEE division.
@@ -98,6 +99,34 @@ constexpr int kMrgWaveBytes = kMrgRows * 18;
 constexpr uint32_t kMrgEmpty = 0xFFFFFFFFu;   // no key (tap offsets are below 2^31)
 constexpr uint32_t kMrgEnd = 0xFFFFFFFFu;     // end of a member list
 constexpr uint32_t kMrgEnd16 = 0xFFFFu;       // the same, as a stored link
+// Binned value gradient (sca_bin_count ... sca_bin_sum): a level map is cut
+// into bins of kBinW x kBinH pixels.  A point's footprint (x0, y0) .. (x0 + 1,
+// y0 + 1) is named by its base (x0 + 1, y0 + 1); a bin's pixels are reached
+// from 8 x 8 bases, of which a row touches 2 x 8 pixels: 16 rows of a matrix
+// instruction.
+constexpr int kBinW = 7, kBinH = 7, kBinRows = kBinH + 1;
+constexpr int kBinPix = kBinW * kBinH;
+// a tile's distinct bins: an open-addressing table in LDS, kept at most 7/8 full
+constexpr int kTabRows = 1024, kTabMax = 896, kTabShift = 32 - 10;
+constexpr uint32_t kTabBytes = (2u * kTabRows + 3u * FLASHSCA_LMAX + 4u) * 4u;
+constexpr uint32_t kTabEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kTileScatter = 0xFFFFFFFFu;   // tile_n of a tile left to the scatter kernel
+// records: word 0 holds the query (23 bits), base column (3) and row (3)
+constexpr int kRecQBits = 23, kRecRowShift = kRecQBits + 3;
+constexpr int kSumChunk = 256, kSumUnroll = 8;
+// A bin of more records is summed in slices of this many, by a workgroup each.
+constexpr int kSumSlice = 1024;
+constexpr int kSumWorkers = 3072;   // wavefronts that take slices in turn (resident ones)
+// words of the workspace header
+enum ScaMisc {
+    kMiscTotal = 0,    // records (64 bits)
+    kMiscList = 2,     // tiles left to the scatter form
+    kMiscFull = 3,     // the records do not fit
+    kMiscSlots = 4,    // slices
+    kMiscMulti = 5,    // bins summed in slices
+    kMiscXcd = 8,      // slices of each XCD's bins
+    kMiscWords = 16
+};
 
 struct ScaParams {
     const void *value;
@@ -143,6 +172,27 @@ struct ScaParams {
     int32_t ord_blocks;
     uint16_t ord_first[kScaOrdMax];
     uint16_t ord_cum[kScaOrdMax + 1];
+    // binned value gradient (null / 0 elsewhere)
+    uint32_t *misc;          // header (ScaMisc)
+    uint32_t *bin_count;     // records per bin
+    uint32_t *bin_start;     // first record of each bin
+    uint32_t *tile_n;        // distinct bins of each tile (kTileScatter: scattered)
+    uint32_t *tile_list;     // tiles left to the scatter kernel
+    uint2 *tile_tab;         // [tile][kTabMax] (bin key, offset within the bin)
+    uint4 *recs;             // records, grouped by bin
+    uint4 *slices;           // [XCD][slice_cap] (bin, first record in the bin, slot, -)
+    uint2 *multi;            // bins summed in slices (bin, first slot)
+    float *partial;          // [slot][pixel][D] sums of a slice
+    uint32_t rec_cap;        // records the workspace holds
+    uint32_t slice_cap;      // slices it holds
+    uint32_t nbins;          // B N heads bpc
+    int32_t bpc;             // bins per camera and head
+    int32_t combos_per_xcd;  // (batch element, camera, head) triples per XCD
+    void *gv_out;            // the value gradient as the caller takes it
+    int32_t gv_dtype;        // its stored type (grad_value is float32 scratch if it is not)
+    int32_t gv_vec;          // its rows take vector stores
+    int32_t level_bin0[FLASHSCA_LMAX], level_nbx[FLASHSCA_LMAX], level_nby[FLASHSCA_LMAX];
+    uint32_t lds_tab;
 };
 
 // LDS: camera matrices [N][12]; level table [5][LMAX]; anchors [Z];
@@ -153,14 +203,19 @@ struct ScaParams {
 // the row-merge table (keys, list heads, row factors, row links
 // [waves * 256] dwords; keys in use [waves * 256] halfwords; a counter).
 struct ScaLds {
-    uint32_t mat, lvl, z, ref, hit, att, gst, tap, mrg, total;
+    uint32_t mat, lvl, z, ref, hit, att, gst, tap, mrg, tab, total;
 };
+
+// LDS of the forward, the scatter-form backward, or the binned backward's
+// count and point kernels.
+enum ScaKind { kScaFwd, kScaScatter, kScaBinned };
 
 __host__ inline uint32_t sca_align16(uint32_t v) { return (v + 15u) & ~15u; }
 
 __host__ ScaLds sca_lds_layout(int N, int Z, int nq_max, int waves, int spw, int LP, int D,
-                               int slot_stride, bool backward)
+                               int slot_stride, ScaKind kind)
 {
+    const bool backward = kind == kScaScatter;
     ScaLds s;
     uint32_t o = 0;
     s.mat = o; o = sca_align16(o + (uint32_t)N * 12u * 4u);
@@ -168,10 +223,11 @@ __host__ ScaLds sca_lds_layout(int N, int Z, int nq_max, int waves, int spw, int
     s.z = o; o = sca_align16(o + (uint32_t)Z * 4u);
     s.ref = o; o = sca_align16(o + (uint32_t)nq_max * N * Z * 8u);
     s.hit = o; o = sca_align16(o + (uint32_t)(nq_max + 1) * 4u);
-    s.att = o; o = sca_align16(o + (backward ? 0u : (uint32_t)waves * spw * LP * 4u));
+    s.att = o; o = sca_align16(o + (kind == kScaFwd ? (uint32_t)waves * spw * LP * 4u : 0u));
     s.gst = o; o = sca_align16(o + (backward ? (uint32_t)waves * spw * D * 4u : 0u));
     s.tap = o; o = sca_align16(o + (uint32_t)waves * spw * slot_stride * 4u);
     s.mrg = o; o = sca_align16(o + (backward ? (uint32_t)waves * kMrgWaveBytes + 16u : 0u));
+    s.tab = o; o = sca_align16(o + (kind == kScaBinned ? kTabBytes : 0u));
     s.total = o;
     return s;
 }
@@ -274,6 +330,22 @@ __device__ __forceinline__ int sca_ordered_qg(const ScaParams &p, int pos)
         else hi = mid;
     }
     return (int)p.ord_first[lo] + (pos - (int)p.ord_cum[lo]);
+}
+
+// Tile number of a tile, and back (the binned value gradient's bookkeeping).
+__device__ __forceinline__ uint32_t sca_tile_id(const ScaParams &p, const ScaTile &t)
+{
+    return (uint32_t)(t.b * p.tiles_per_b + t.qg * p.heads + t.head);
+}
+
+__device__ __forceinline__ ScaTile sca_tile_of(const ScaParams &p, uint32_t id)
+{
+    ScaTile t;
+    t.b = (int)id / p.tiles_per_b;
+    const int tb = (int)id - t.b * p.tiles_per_b;
+    t.qg = tb / p.heads;
+    t.head = tb - t.qg * p.heads;
+    return t;
 }
 
 __device__ __forceinline__ ScaTile sca_tile(const ScaParams &p)
@@ -452,17 +524,17 @@ __device__ __forceinline__ void sca_softmax_stats(const ScaParams &p, const ScaS
     rcp = 1.0f / sum;
 }
 
-// Set-up of point j of a slot in one camera: tap byte offsets (kScaNoTap
-// outside the map) and the location's fractions.  Returns false when no
-// corner lies inside the map (all taps kScaNoTap).
-__device__ __forceinline__ bool sca_setup_point(const ScaParams &p, const ScaSmem &m,
-                                                const float2 *ref, const ScaSlot &s, int j,
-                                                uint32_t head_off, uint4 &o, float &ax,
-                                                float &ay)
+// Location of point j of a slot in one camera: level, first tap and
+// fractions.  Returns false when no corner lies inside the map (the location
+// is then not usable: it may be past every map or not a number).
+struct ScaLoc {
+    int l, x0, y0;
+    float ax, ay;
+};
+
+__device__ __forceinline__ bool sca_locate(const ScaParams &p, const ScaSmem &m,
+                                           const float2 *ref, const ScaSlot &s, int j, ScaLoc &c)
 {
-    o = make_uint4(kScaNoTap, kScaNoTap, kScaNoTap, kScaNoTap);
-    ax = 0.0f;
-    ay = 0.0f;
     const int l = div_small(j, p.P, p.rcp_p);
     const int k = j - l * p.P;
     const int zk = k - div_small(k, p.Z, p.rcp_z) * p.Z;   // anchor k mod Z
@@ -475,20 +547,49 @@ __device__ __forceinline__ bool sca_setup_point(const ScaParams &p, const ScaSme
     sy = sy + dxy.y;
     const float xim = sx - 0.5f;
     const float yim = sy - 0.5f;
-    if (!(xim > -1.0f && xim < Wl && yim > -1.0f && yim < Hl)) return false;
+    // no branches: x and y are loaded and located together
     const float x0f = floorf(xim), y0f = floorf(yim);
-    ax = xim - x0f;
-    ay = yim - y0f;
-    const int x0 = (int)x0f, y0 = (int)y0f;
-    const int wi = m.lw[l], hi = m.lh[l];
-    const bool xl = x0 >= 0, xr = x0 + 1 < wi;
-    const bool yt = y0 >= 0, yb = y0 + 1 < hi;
-    const int row = (int)m.lst[l] + y0 * wi + x0;
+    c.l = l;
+    c.ax = xim - x0f;
+    c.ay = yim - y0f;
+    c.x0 = (int)x0f;
+    c.y0 = (int)y0f;
+    return (xim > -1.0f) & (xim < Wl) & (yim > -1.0f) & (yim < Hl);
+}
+
+// Tap byte offsets of a location (kScaNoTap outside the map).
+__device__ __forceinline__ uint4 sca_tap_offsets(const ScaParams &p, const ScaSmem &m,
+                                                 const ScaLoc &c, uint32_t head_off)
+{
+    uint4 o = make_uint4(kScaNoTap, kScaNoTap, kScaNoTap, kScaNoTap);
+    const int wi = m.lw[c.l], hi = m.lh[c.l];
+    const bool xl = c.x0 >= 0, xr = c.x0 + 1 < wi;
+    const bool yt = c.y0 >= 0, yb = c.y0 + 1 < hi;
+    const int row = (int)m.lst[c.l] + c.y0 * wi + c.x0;
     const uint32_t rb = p.row_bytes;
     if (xl && yt) o.x = (uint32_t)row * rb + head_off;
     if (xr && yt) o.y = (uint32_t)(row + 1) * rb + head_off;
     if (xl && yb) o.z = (uint32_t)(row + wi) * rb + head_off;
     if (xr && yb) o.w = (uint32_t)(row + wi + 1) * rb + head_off;
+    return o;
+}
+
+// Set-up of point j of a slot in one camera: tap byte offsets (kScaNoTap
+// outside the map) and the location's fractions.  Returns false when no
+// corner lies inside the map (all taps kScaNoTap).
+__device__ __forceinline__ bool sca_setup_point(const ScaParams &p, const ScaSmem &m,
+                                                const float2 *ref, const ScaSlot &s, int j,
+                                                uint32_t head_off, uint4 &o, float &ax,
+                                                float &ay)
+{
+    o = make_uint4(kScaNoTap, kScaNoTap, kScaNoTap, kScaNoTap);
+    ax = 0.0f;
+    ay = 0.0f;
+    ScaLoc c;
+    if (!sca_locate(p, m, ref, s, j, c)) return false;
+    o = sca_tap_offsets(p, m, c, head_off);
+    ax = c.ax;
+    ay = c.ay;
     return true;
 }
 
@@ -647,10 +748,9 @@ enum ScaPhaseSlot {
 #define SPH_WRITE(lane) ((void)0)
 #endif
 
-// Backward: gradients of value (scatter), offsets and logits.
+// Backward, scatter form: gradients of value, offsets and logits of one tile.
 template <int DT, int LW>
-__global__ void __launch_bounds__(kScaBwdThreads)
-sca_bwd(const ScaParams p)
+__device__ __forceinline__ void sca_bwd_tile(const ScaParams &p, const ScaTile tl)
 {
     constexpr int ES = ElemSize<DT>::value;
     constexpr int EPV = LW / ES;
@@ -662,7 +762,6 @@ sca_bwd(const ScaParams p)
     const int nthreads = blockDim.x;
 
     SPH_DECL;
-    const ScaTile tl = sca_tile(p);
     const int b = tl.b;
     const int r_first = tl.qg * p.tile_pairs;   // first query rank of the tile
     sca_project_tile(p, m, b, r_first);
@@ -922,6 +1021,798 @@ sca_bwd(const ScaParams p)
     SPH_WRITE(lane);
 }
 
+template <int DT, int LW>
+__global__ void __launch_bounds__(kScaBwdThreads)
+sca_bwd(const ScaParams p)
+{
+    sca_bwd_tile<DT, LW>(p, sca_tile(p));
+}
+
+// The scatter form over the tiles that the binned value gradient left (value
+// gradient only): every tile when the records did not fit the workspace, else
+// those whose points fall into too many bins.  Usually there are none.
+template <int DT, int LW>
+__global__ void __launch_bounds__(kScaBwdThreads)
+sca_bwd_left(const ScaParams p)
+{
+    const bool all = p.misc[kMiscFull] != 0u;
+    const uint32_t n = all ? (uint32_t)(p.B * p.tiles_per_b) : p.misc[kMiscList];
+    for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
+        sca_bwd_tile<DT, LW>(p, sca_tile_of(p, all ? k : p.tile_list[k]));
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Binned backward.
+//
+// The scatter form's value gradient is bound by global float atomics, which
+// retire at 1.3 TB/s whatever their locality or width, and by the LDS chains
+// of its row merge.  Here the value gradient takes no float atomics: the
+// points are grouped by pixel bin, and each bin is summed and written once.
+//   * sca_bin_count: counts the points of each bin.  A tile collects its bins
+//     in an LDS table first; one integer atomic per (tile, bin) adds its count
+//     and returns the tile's offset within the bin, kept for sca_bwd_points.
+//   * sca_bin_alloc: gives every bin its range of the record array.
+//   * sca_bwd_points: the offset and logit gradients, and a 16-byte record
+//     (query, base, fractions, mean * a_j) of every point to each bin its
+//     footprint touches (1.2 on average).
+//   * sca_bin_sum: sums each bin's records into its pixels in LDS and writes
+//     them, zeros included.
+//   * sca_bwd_left: adds the tiles that could not be binned (usually none).
+// ---------------------------------------------------------------------------
+struct ScaTab {
+    uint32_t *key, *val;
+    int32_t *bin0, *nbx, *nby;
+    uint32_t *n;   // entries in use, a flag that some bin did not fit
+};
+
+__device__ __forceinline__ ScaTab sca_tab(const ScaParams &p, unsigned char *smem)
+{
+    ScaTab t;
+    t.key = reinterpret_cast<uint32_t *>(smem + p.lds_tab);
+    t.val = t.key + kTabRows;
+    t.bin0 = reinterpret_cast<int32_t *>(t.val + kTabRows);
+    t.nbx = t.bin0 + FLASHSCA_LMAX;
+    t.nby = t.nbx + FLASHSCA_LMAX;
+    t.n = reinterpret_cast<uint32_t *>(t.nby + FLASHSCA_LMAX);
+    return t;
+}
+
+__device__ __forceinline__ void sca_tab_init(const ScaParams &p, const ScaTab &t)
+{
+    for (int h = threadIdx.x; h < kTabRows; h += blockDim.x) {
+        t.key[h] = kTabEmpty;
+        t.val[h] = 0u;
+    }
+    if (threadIdx.x < FLASHSCA_LMAX) {
+        t.bin0[threadIdx.x] = p.level_bin0[threadIdx.x];
+        t.nbx[threadIdx.x] = p.level_nbx[threadIdx.x];
+        t.nby[threadIdx.x] = p.level_nby[threadIdx.x];
+    }
+    if (threadIdx.x < 2) t.n[threadIdx.x] = 0u;
+}
+
+__device__ __forceinline__ uint32_t sca_tab_hash(uint32_t key)
+{
+    return (key * 0x9E3779B1u) >> kTabShift;
+}
+
+// The bins that hold a pixel of the location's footprint: f(key, column, row)
+// with the bin's key (n heads bpc + bin) and the base within the bin.  A base
+// on a bin's first column (row) also reaches the last pixel column (row) of
+// the bin before it.
+template <class F>
+__device__ __forceinline__ void sca_point_bins(const ScaParams &p, const ScaTab &t,
+                                               const ScaLoc &c, int n, F f)
+{
+    const int X = c.x0 + 1, Y = c.y0 + 1;
+    const int nbx = t.nbx[c.l], nby = t.nby[c.l];
+    // X / 7 and Y / 7, exact below 2^15
+    const int bx = (int)(((uint32_t)X * 37450u) >> 18), col = X - bx * kBinW;
+    const int by = (int)(((uint32_t)Y * 37450u) >> 18);
+    const int row = Y - by * kBinH;
+    const uint32_t key0 = (uint32_t)(n * p.heads * p.bpc + t.bin0[c.l]);
+    const uint32_t key = key0 + (uint32_t)(by * nbx + bx);
+    const bool left = col == 0 && bx > 0, up = row == 0 && by > 0;
+    if (bx < nbx && by < nby) f(key, col, row);
+    if (left && by < nby) f(key - 1u, kBinW, row);
+    if (up && bx < nbx) f(key - (uint32_t)nbx, col, kBinH);
+    if (left && up) f(key - (uint32_t)nbx - 1u, kBinW, kBinH);
+}
+
+__global__ void __launch_bounds__(kScaBwdThreads) sca_bin_count(const ScaParams p)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const ScaSmem m = sca_smem(p, smem);
+    const ScaTab t = sca_tab(p, smem);
+    const int wave = threadIdx.x / kScaWave;
+    const int lane = threadIdx.x % kScaWave;
+    const ScaTile tl = sca_tile(p);
+    const int r_first = tl.qg * p.tile_pairs;
+    sca_tab_init(p, t);
+    sca_project_tile(p, m, tl.b, r_first);   // ends with a workgroup barrier
+    const ScaSlot s = sca_slot(p, m, tl.b, r_first, tl.head, wave, lane);
+    const uint32_t cams = sca_wave_cameras(p, s.hits);
+    for (int c0 = 0; c0 < p.LP; c0 += p.lph) {
+        const int j = c0 + s.sub;
+        for (int n = 0; n < p.N; ++n) {
+            if (!((cams >> n) & 1u)) continue;
+            if (!((s.hits >> n) & 1u) || j >= p.LP) continue;
+            ScaLoc c;
+            if (!sca_locate(p, m, m.ref + (size_t)(s.qi * p.N + n) * p.Z, s, j, c)) continue;
+            sca_point_bins(p, t, c, n, [&](uint32_t key, int, int) {
+                uint32_t h = sca_tab_hash(key);
+                for (int probe = 0; probe < kTabRows; ++probe) {
+                    uint32_t old = t.key[h];
+                    if (old == kTabEmpty) old = atomicCAS(&t.key[h], kTabEmpty, key);
+                    if (old == kTabEmpty && atomicAdd(&t.n[0], 1u) >= (uint32_t)kTabMax)
+                        t.n[1] = 1u;
+                    if (old == kTabEmpty || old == key) {
+                        atomicAdd(&t.val[h], 1u);
+                        return;
+                    }
+                    h = (h + 1) & (uint32_t)(kTabRows - 1);
+                }
+                t.n[1] = 1u;
+            });
+        }
+    }
+    __syncthreads();
+    const uint32_t tile = sca_tile_id(p, tl);
+    if (t.n[1]) {
+        if (threadIdx.x == 0) {
+            p.tile_n[tile] = kTileScatter;
+            p.tile_list[atomicAdd(&p.misc[kMiscList], 1u)] = tile;
+        }
+        return;
+    }
+    if (threadIdx.x == 0) {
+        p.tile_n[tile] = t.n[0];
+        t.n[2] = 0u;
+    }
+    __syncthreads();
+    const uint32_t base = (uint32_t)((tl.b * p.N * p.heads + tl.head) * p.bpc);
+    for (int h = threadIdx.x; h < kTabRows; h += blockDim.x) {
+        const uint32_t key = t.key[h];
+        if (key == kTabEmpty) continue;
+        const uint32_t off = atomicAdd(&p.bin_count[base + key], t.val[h]);
+        p.tile_tab[(size_t)tile * kTabMax + atomicAdd(&t.n[2], 1u)] = make_uint2(key, off);
+    }
+}
+
+__global__ void __launch_bounds__(256) sca_bin_alloc(const ScaParams p)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    const int lane = threadIdx.x % kScaWave;
+    const unsigned long long n = i < p.nbins ? p.bin_count[i] : 0u;
+    unsigned long long inc = n;
+    for (int o = 1; o < kScaWave; o <<= 1) {
+        const unsigned long long v = __shfl_up(inc, o);
+        inc += lane >= o ? v : 0ull;
+    }
+    unsigned long long first = 0;
+    if (lane == kScaWave - 1)
+        first = atomicAdd(reinterpret_cast<unsigned long long *>(p.misc + kMiscTotal), inc);
+    first = __shfl(first, kScaWave - 1) + inc - n;
+    if (i < p.nbins) p.bin_start[i] = (uint32_t)first;
+    if (first + n > p.rec_cap) p.misc[kMiscFull] = 1u;
+    // Slices of the large bins.  One atomic per wavefront and counter:
+    // returning atomics on one address take their turns (42 us in place of 5
+    // with one per bin).
+    const bool many = n > (uint32_t)kSumSlice && first + n <= p.rec_cap;
+    const uint64_t bins = __ballot(many);
+    if (!bins) return;
+    const uint32_t ns = many ? ((uint32_t)n + kSumSlice - 1) / kSumSlice : 0u;
+    uint32_t upto = ns;
+    for (int o = 1; o < kScaWave; o <<= 1) {
+        const uint32_t v = __shfl_up(upto, o);
+        upto += lane >= o ? v : 0u;
+    }
+    const uint32_t all = __shfl(upto, kScaWave - 1);
+    // the XCD of the wavefront's first such bin, for all of them
+    const int lead = (int)__builtin_ctzll(bins);
+    const uint32_t m = i / (uint32_t)p.bpc;   // (b N + n) heads + head
+    const uint32_t combo = (m % (uint32_t)p.heads) * (uint32_t)(p.B * p.N) + m / (uint32_t)p.heads;
+    const uint32_t x = __shfl(combo / (uint32_t)p.combos_per_xcd, lead);
+    uint32_t slot = 0, at = 0, mb = 0;
+    if (lane == lead) {
+        slot = atomicAdd(&p.misc[kMiscSlots], all);
+        mb = atomicAdd(&p.misc[kMiscMulti], (uint32_t)__popcll(bins));
+        at = atomicAdd(&p.misc[kMiscXcd + x], all);
+    }
+    slot = __shfl(slot, lead) + upto - ns;
+    at = __shfl(at, lead) + upto - ns;
+    mb = __shfl(mb, lead) + (uint32_t)__popcll(bins & ((1ull << lane) - 1ull));
+    if (!many) return;
+    if (slot + ns > p.slice_cap || at + ns > p.slice_cap || mb >= p.slice_cap) {
+        p.misc[kMiscFull] = 1u;
+        return;
+    }
+    p.multi[mb] = make_uint2(i, slot);
+    for (uint32_t j = 0; j < ns; ++j)
+        p.slices[(size_t)x * p.slice_cap + at + j] = make_uint4(i, j * kSumSlice, slot + j, 0u);
+}
+
+// Offset and logit gradients, and the records of the value gradient
+// (p.recs; null: none wanted).  LPH lanes per slot.
+template <int DT, int LW, int LPH>
+__global__ void __launch_bounds__(kScaBwdThreads, 4)
+sca_bwd_points(const ScaParams p)
+{
+    constexpr int ES = ElemSize<DT>::value;
+    constexpr int EPV = LW / ES;
+    constexpr int NB = LPH / 8;   // batches of 8 points per chunk
+    extern __shared__ __align__(16) unsigned char smem[];
+    const ScaSmem m = sca_smem(p, smem);
+    const ScaTab tab = sca_tab(p, smem);
+    const int wave = threadIdx.x / kScaWave;
+    const int lane = threadIdx.x % kScaWave;
+    const ScaTile tl = sca_tile(p);
+    const int b = tl.b;
+    const int r_first = tl.qg * p.tile_pairs;
+    const uint32_t tile = sca_tile_id(p, tl);
+    bool emit = p.recs != nullptr;
+    uint32_t nkeys = 0;
+    if (emit) {
+        nkeys = p.tile_n[tile];
+        emit = nkeys != kTileScatter && p.misc[kMiscFull] == 0u;
+        sca_tab_init(p, tab);
+    }
+    sca_project_tile(p, m, b, r_first);   // ends with a workgroup barrier
+    if (emit) {
+        // the tile's bins again, with the position of its next record in each
+        const uint32_t base = (uint32_t)((b * p.N * p.heads + tl.head) * p.bpc);
+        for (uint32_t k = threadIdx.x; k < nkeys; k += blockDim.x) {
+            const uint2 e = p.tile_tab[(size_t)tile * kTabMax + k];
+            uint32_t h = sca_tab_hash(e.x);
+            while (atomicCAS(&tab.key[h], kTabEmpty, e.x) != kTabEmpty)
+                h = (h + 1) & (uint32_t)(kTabRows - 1);
+            tab.val[h] = p.bin_start[base + e.x] + e.y;
+        }
+        __syncthreads();
+    }
+
+    const ScaSlot s = sca_slot(p, m, b, r_first, tl.head, wave, lane);
+    const int LP = p.LP;
+    float mx, rcp;
+    sca_softmax_stats(p, s, mx, rcp);
+    const uint32_t cams = sca_wave_cameras(p, s.hits);
+    const int e0 = s.sub * EPV;
+    float gs[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+        gs[e] = (s.hits && e0 + e < p.D)
+                    ? p.grad_out[((size_t)b * p.Q + s.q) * (size_t)p.C + (size_t)s.mh * p.D + e0 + e]
+                    : 0.0f;
+    }
+    const uint32_t lane_off = (uint32_t)s.sub * LW;
+    const uint32_t head_off = (uint32_t)s.mh * p.head_bytes;
+    uint32_t *rec = m.tap + (size_t)(wave * p.spw + s.slot) * p.slot_stride;
+
+    float dot = 0.0f;   // sum of a_j d a_j over this lane's points
+    for (int c0 = 0; c0 < LP; c0 += LPH) {
+        const int j = c0 + s.sub;
+        const bool own = s.hits && j < LP;
+        const float a_j = own ? expf(p.logits[s.pt0 + j] - mx) * rcp : 0.0f;
+        float g_da = 0.0f, g_dx = 0.0f, g_dy = 0.0f;
+        for (int n = 0; n < p.N; ++n) {
+            if (!((cams >> n) & 1u)) continue;
+            const __amdgpu_buffer_rsrc_t rsrc = sca_camera_rsrc(p, b, n);
+            uint4 o = make_uint4(kScaNoTap, kScaNoTap, kScaNoTap, kScaNoTap);
+            ScaLoc c;
+            float ax = 0.0f, ay = 0.0f;
+            if (own && ((s.hits >> n) & 1u) &&
+                sca_locate(p, m, m.ref + (size_t)(s.qi * p.N + n) * p.Z, s, j, c)) {
+                o = sca_tap_offsets(p, m, c, head_off);
+                ax = c.ax;
+                ay = c.ay;
+                if (emit) {
+                    const float aa = s.inv * a_j;
+                    sca_point_bins(p, tab, c, n, [&](uint32_t key, int col, int row) {
+                        uint32_t h = sca_tab_hash(key);
+                        for (int probe = 0; probe < kTabRows && tab.key[h] != key; ++probe)
+                            h = (h + 1) & (uint32_t)(kTabRows - 1);
+                        const uint32_t at = atomicAdd(&tab.val[h], 1u);
+                        const uint32_t w = (uint32_t)s.q | ((uint32_t)(row * 8 + col) << kRecQBits);
+                        if (at < p.rec_cap)
+                            p.recs[at] = make_uint4(w, __builtin_bit_cast(uint32_t, c.ax),
+                                                    __builtin_bit_cast(uint32_t, c.ay),
+                                                    __builtin_bit_cast(uint32_t, aa));
+                    });
+                }
+            }
+            uint32_t *mine_rec = rec + s.sub * kRecBwd;
+            *reinterpret_cast<uint4 *>(mine_rec) = o;
+            *reinterpret_cast<float2 *>(mine_rec + 4) = make_float2(ax, ay);
+            wave_lds_sync();
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                if (NB > 1 && c0 + 8 * h >= LP) break;
+                float da[8], dx[8], dy[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const uint32_t *r = rec + (8 * h + t) * kRecBwd;
+                    const uint4 to = *reinterpret_cast<const uint4 *>(r);
+                    const float2 tf = *reinterpret_cast<const float2 *>(r + 4);
+                    const Raw<LW> v0 = load_vec<LW>(rsrc, to.x + lane_off, 0);
+                    const Raw<LW> v1 = load_vec<LW>(rsrc, to.y + lane_off, 0);
+                    const Raw<LW> v2 = load_vec<LW>(rsrc, to.z + lane_off, 0);
+                    const Raw<LW> v3 = load_vec<LW>(rsrc, to.w + lane_off, 0);
+                    float d0 = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) {
+                        d0 = fmaf(elem<DT, LW>(v0, e), gs[e], d0);
+                        d1 = fmaf(elem<DT, LW>(v1, e), gs[e], d1);
+                        d2 = fmaf(elem<DT, LW>(v2, e), gs[e], d2);
+                        d3 = fmaf(elem<DT, LW>(v3, e), gs[e], d3);
+                    }
+                    // the point's gradients are linear in the four dot
+                    // products: a lane forms its share of each
+                    const float top = (1.0f - tf.x) * d0 + tf.x * d1;
+                    const float bot = (1.0f - tf.x) * d2 + tf.x * d3;
+                    da[t] = (1.0f - tf.y) * top + tf.y * bot;
+                    dx[t] = (1.0f - tf.y) * (d1 - d0) + tf.y * (d3 - d2);
+                    dy[t] = bot - top;
+                    // two points' loads in flight: more would not fit the registers
+                    if (t & 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                // Sums over the slot's lanes, each lane keeping one point:
+                // halves are exchanged, so 8 points x 3 sums take 21 shuffles
+                // in place of 72.
+                if constexpr (LPH == 16) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        da[t] += __shfl_xor(da[t], 8);
+                        dx[t] += __shfl_xor(dx[t], 8);
+                        dy[t] += __shfl_xor(dy[t], 8);
+                    }
+                }
+#pragma unroll
+                for (int w = 4; w >= 1; w >>= 1) {
+                    const bool hi = (s.sub & w) != 0;
+#pragma unroll
+                    for (int t = 0; t < w; ++t) {
+                        const float sa = hi ? da[t] : da[t + w], ka = hi ? da[t + w] : da[t];
+                        const float sx = hi ? dx[t] : dx[t + w], kx = hi ? dx[t + w] : dx[t];
+                        const float sy = hi ? dy[t] : dy[t + w], ky = hi ? dy[t + w] : dy[t];
+                        da[t] = ka + __shfl_xor(sa, w);
+                        dx[t] = kx + __shfl_xor(sx, w);
+                        dy[t] = ky + __shfl_xor(sy, w);
+                    }
+                }
+                if (NB == 1 || (s.sub >> 3) == h) {
+                    g_da += da[0];
+                    g_dx += dx[0];
+                    g_dy += dy[0];
+                }
+            }
+            wave_lds_sync();
+        }
+        if (own) {
+            dot += a_j * g_da;
+            const float sa = s.inv * a_j;
+            if (p.grad_offsets)
+                reinterpret_cast<float2 *>(p.grad_offsets)[s.pt0 + j] =
+                    make_float2(sa * g_dx, sa * g_dy);
+            // d a_j for now; the softmax backward below finishes it
+            if (p.grad_logits) p.grad_logits[s.pt0 + j] = g_da;
+        }
+    }
+    for (int x = LPH >> 1; x >= 1; x >>= 1) dot += __shfl_xor(dot, x);
+    if (s.active) {
+        for (int j = s.sub; j < LP; j += LPH) {
+            if (s.hits) {
+                if (p.grad_logits) {
+                    const float sa = s.inv * (expf(p.logits[s.pt0 + j] - mx) * rcp);
+                    p.grad_logits[s.pt0 + j] = sa * (p.grad_logits[s.pt0 + j] - dot);
+                }
+            } else {
+                if (p.grad_logits) p.grad_logits[s.pt0 + j] = 0.0f;
+                if (p.grad_offsets)
+                    reinterpret_cast<float2 *>(p.grad_offsets)[s.pt0 + j] = make_float2(0.0f, 0.0f);
+            }
+        }
+    }
+}
+
+// float32 to the 16-bit storage type, rounded once to nearest even
+__device__ __forceinline__ uint16_t sca_to_half(const ScaParams &p, float v)
+{
+    return p.gv_dtype == FLASHBEV_F16 ? __builtin_bit_cast(uint16_t, (_Float16)v)
+                                      : __builtin_bit_cast(uint16_t, (__bf16)v);
+}
+
+// EPL consecutive floats at byte offset `off` of a buffer
+template <int EPL>
+__device__ __forceinline__ void load_floats(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                            float (&g)[EPL])
+{
+    constexpr int V = EPL % 2 == 0 ? 2 : 1;
+#pragma unroll
+    for (int e = 0; e < EPL; e += V) {
+        const Raw<4 * V> v = load_vec<4 * V>(rsrc, off, (uint32_t)(e * 4));
+#pragma unroll
+        for (int k = 0; k < V; ++k) g[e + k] = __builtin_bit_cast(float, v.w[k]);
+    }
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Sums of one bin by one wavefront, SW channels at a time, on the matrix
+// cores.  A chunk of records is sorted in LDS by base row.  A base row touches
+// 2 pixel rows x 8 pixel columns, the 16 rows of v_mfma_f32_16x16x4_f32, whose
+// A operand is four records' weights on those pixels and whose B operand their
+// output-gradient rows, 16 channels at a time: every record costs the same,
+// however the points crowd.  A base row's sums go to the bin's pixels in LDS
+// when the next row begins; they are this wavefront's own, so there are no
+// atomics and no barriers.  (ds_add_f32 retires 0.33 lanes per clock and CU on
+// this chip.)  Measured at BEVFormer-base, P = 8: 385 us for 13 M records,
+// matrix units busy for 90 us of it, vector issue for about 150; the same sums
+// by groups of lanes, one base each, took 525 us, most lanes waiting for the
+// fullest base.
+template <int SW>
+struct ScaSum {
+    static constexpr int NT = (SW + 15) / 16;        // channels per lane
+    static constexpr int kOut = kBinPix * SW;        // floats of a bin's sums
+    static constexpr int kRecs = kSumChunk + 3 * kBinRows;   // rows padded to fours
+    static constexpr int kBytes = kOut * 4 + 16 + kRecs * 16 + 64;
+    static constexpr int kRecOff = (kOut * 4 + 15) / 16 * 16;
+};
+
+// Where a bin lies.
+struct ScaBin {
+    int head, bn, l, px0, py0;
+};
+
+__device__ __forceinline__ ScaBin sca_bin_of(const ScaParams &p, uint32_t gb)
+{
+    ScaBin q;
+    const int m = (int)(gb / (uint32_t)p.bpc), bin = (int)gb - m * p.bpc;
+    q.bn = m / p.heads;
+    q.head = m - q.bn * p.heads;
+    q.l = 0;
+    for (int l = 1; l < p.L; ++l)
+        if (bin >= p.level_bin0[l]) q.l = l;
+    const int r = bin - p.level_bin0[q.l];
+    const int by = r / p.level_nbx[q.l];
+    q.py0 = by * kBinH;
+    q.px0 = (r - by * p.level_nbx[q.l]) * kBinW;
+    return q;
+}
+
+// Adds a base row's sums: acc[t][v] of lane (g, n) is pixel row
+// row - 1 + g / 2, column 4 (g mod 2) + v - 1, channel n NT + t.
+template <int SW>
+__device__ __forceinline__ void sca_bin_flush(float *out, int row, int lane,
+                                              v4f (&acc)[ScaSum<SW>::NT])
+{
+    constexpr int NT = ScaSum<SW>::NT;
+    const int g = lane >> 4, n = lane & 15;
+    const int y = row - 1 + (g >> 1);
+    const int x = 4 * (g & 1) - 1;
+    if (y >= 0 && y < kBinH && n * NT < SW) {
+        float *o = out + (y * kBinW + x) * SW + n * NT;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (v > 0 || x >= 0) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) o[v * SW + t] += acc[t][v];
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    wave_lds_sync();
+}
+
+// out[pixel][SW] = sums over n records from `recs` on, channels c0 ... of the
+// bin's head.
+template <int SW>
+__device__ __forceinline__ void sca_bin_records(const ScaParams &p, unsigned char *smem,
+                                                const ScaBin &bin, int c0, const uint4 *recs,
+                                                uint32_t n)
+{
+    using S = ScaSum<SW>;
+    constexpr int NT = S::NT;
+    float *out = reinterpret_cast<float *>(smem);
+    uint4 *rec = reinterpret_cast<uint4 *>(smem + S::kRecOff);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(rec + S::kRecs);
+    const int lane = threadIdx.x;
+    const uint32_t row_bytes = (uint32_t)p.C * 4u;
+    const float *gout = p.grad_out + (size_t)(bin.bn / p.N) * p.Q * p.C;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(gout), (short)0, (int)((uint32_t)p.Q * row_bytes), 0x00020000);
+    const uint32_t head_off = (uint32_t)(bin.head * p.D + c0) * 4u;
+    const int nn = lane & 15, kk = lane >> 4;
+    const uint32_t lane_off = (uint32_t)(nn * NT) * 4u;
+    const bool idle = nn * NT >= SW;   // lanes past the channels load nothing
+    const int j = lane & 7;            // A operand: pixel column + 1
+    const bool bottom = (lane & 8) != 0;
+    constexpr int PL = kSumChunk / kScaWave;
+    constexpr uint32_t kQMask = (1u << kRecQBits) - 1u;
+    uint4 r[PL];
+#pragma unroll
+    for (int q = 0; q < PL; ++q) {
+        const uint32_t i = (uint32_t)(q * kScaWave + lane);
+        r[q] = i < n ? recs[i] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    for (int i = lane * 4; i < S::kOut; i += kScaWave * 4)
+        *reinterpret_cast<v4f *>(out + i) = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    float bad = 0.0f;   // NaN once a gradient value is not finite
+    for (uint32_t at = 0; at < n; at += kSumChunk) {
+        // ---- counting sort of the chunk by base row, rows padded to fours
+        uint32_t rank[PL];
+        if (lane < kBinRows) cnt[lane] = 0u;
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            rank[q] = 0u;
+            if (at + (uint32_t)(q * kScaWave + lane) < n)
+                rank[q] = atomicAdd(&cnt[r[q].x >> kRecRowShift], 1u);
+        }
+        wave_lds_sync();
+        // lane c holds row c's first position, lane kBinRows the end
+        const uint32_t have = lane < kBinRows ? cnt[lane] : 0u;
+        const uint32_t room = (have + 3u) & ~3u;
+        uint32_t first = room;
+#pragma unroll
+        for (int o = 1; o < 2 * kBinRows; o <<= 1) {
+            const uint32_t v = __shfl_up(first, o);
+            first += lane >= o ? v : 0u;
+        }
+        first -= room;
+        wave_lds_sync();
+        if (lane < kBinRows) {
+            cnt[lane] = first;
+            for (uint32_t k = first + have; k < first + room; ++k)
+                rec[k] = make_uint4(kScaNoTap, 0u, 0u, 0u);
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            if (at + (uint32_t)(q * kScaWave + lane) >= n) continue;
+            // gradient row offset (a multiple of 32) with the base column, x
+            // fraction, factor times the row weights
+            const float fy = __builtin_bit_cast(float, r[q].z);
+            const float a = __builtin_bit_cast(float, r[q].w);
+            rec[cnt[r[q].x >> kRecRowShift] + rank[q]] =
+                make_uint4(((r[q].x & kQMask) * row_bytes + head_off) |
+                               ((r[q].x >> kRecQBits) & 7u),
+                           r[q].y, __builtin_bit_cast(uint32_t, a * (1.0f - fy)),
+                           __builtin_bit_cast(uint32_t, a * fy));
+        }
+        // the next chunk's records, in flight during this one's sums
+        if (at + kSumChunk < n) {
+#pragma unroll
+            for (int q = 0; q < PL; ++q) {
+                const uint32_t i = at + kSumChunk + (uint32_t)(q * kScaWave + lane);
+                r[q] = i < n ? recs[i] : make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
+        wave_lds_sync();
+        // ---- four records per step, the next steps' gradient rows in flight
+        const int steps = __builtin_amdgcn_readlane((int)first, kBinRows) >> 2;
+        v4f acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        int row = 0;
+        int next = __builtin_amdgcn_readlane((int)first, 1) >> 2;   // first step of row + 1
+        float w[kSumUnroll], g[kSumUnroll][NT];
+        const auto fetch = [&](int s0) {
+            uint4 e[kSumUnroll];
+#pragma unroll
+            for (int u = 0; u < kSumUnroll; ++u) e[u] = rec[4 * min(s0 + u, steps - 1) + kk];
+#pragma unroll
+            for (int u = 0; u < kSumUnroll; ++u) {
+                uint32_t off = (e[u].x & ~15u) + lane_off;
+                if constexpr (SW % 16 != 0) off |= idle ? kScaNoTap : 0u;
+                load_floats<NT>(rsrc, off, g[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kSumUnroll; ++u) {
+                const float fx = __builtin_bit_cast(float, e[u].y);
+                const float wy = __builtin_bit_cast(float, bottom ? e[u].w : e[u].z);
+                const int d = j - (int)(e[u].x & 15u);
+                // both products first: selects, not branches
+                const float wl = wy * (1.0f - fx), wr = wy * fx;
+                const float v = d == 1 ? wr : 0.0f;
+                w[u] = d == 0 ? wl : v;
+            }
+        };
+        fetch(0);
+        for (int s0 = 0; s0 < steps; s0 += kSumUnroll) {
+            float a[kSumUnroll], b[kSumUnroll][NT];
+#pragma unroll
+            for (int u = 0; u < kSumUnroll; ++u) {
+                a[u] = w[u];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    b[u][t] = g[u][t];
+                    bad = fmaf(0.0f, g[u][t], bad);
+                }
+            }
+            if (s0 + kSumUnroll < steps) fetch(s0 + kSumUnroll);
+#pragma unroll
+            for (int u = 0; u < kSumUnroll; ++u) {
+                if (s0 + u < steps) {
+                    while (s0 + u >= next) {
+                        sca_bin_flush<SW>(out, row, lane, acc);
+                        ++row;
+                        next = __builtin_amdgcn_readlane((int)first, row + 1) >> 2;
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[u][t], acc[t], 0, 0, 0);
+                }
+            }
+        }
+        sca_bin_flush<SW>(out, row, lane, acc);
+    }
+    if (!__ballot(bad != 0.0f)) return;
+    // A gradient value is not finite: its product with a zero weight has
+    // reached other pixels.  Sum again, each record onto its own pixels.
+    for (int i = lane; i < S::kOut; i += kScaWave) out[i] = 0.0f;
+    wave_lds_sync();
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint4 q = recs[i];
+        const int y0 = (int)(q.x >> kRecRowShift) - 1, x0 = (int)((q.x >> kRecQBits) & 7u) - 1;
+        const float fx = __builtin_bit_cast(float, q.y), fy = __builtin_bit_cast(float, q.z);
+        const float a = __builtin_bit_cast(float, q.w);
+        if (lane < SW) {
+            const float v = gout[(size_t)(q.x & kQMask) * p.C + bin.head * p.D + c0 + lane];
+            for (int t = 0; t < 4; ++t) {
+                const int y = y0 + (t >> 1), x = x0 + (t & 1);
+                if (y >= 0 && y < kBinH && x >= 0 && x < kBinW)
+                    out[(y * kBinW + x) * SW + lane] +=
+                        a * ((t & 2) ? fy : 1.0f - fy) * ((t & 1) ? fx : 1.0f - fx) * v;
+            }
+        }
+    }
+    wave_lds_sync();
+}
+
+// V channels of the value gradient at element `at`: as the caller takes it,
+// or as float32 where tiles are still to be added (f32).
+template <int V>
+__device__ __forceinline__ void sca_put(const ScaParams &p, uint64_t at, const float (&s)[V], bool f32)
+{
+    if (f32) {
+        float *o = p.grad_value + at;
+        if (V == 4 && p.gv_vec) {
+            *reinterpret_cast<v4f *>(o) = v4f{s[0], s[V > 1 ? 1 : 0], s[V > 2 ? 2 : 0], s[V - 1]};
+        } else {
+#pragma unroll
+            for (int t = 0; t < V; ++t) o[t] = s[t];
+        }
+        return;
+    }
+    uint16_t *o = static_cast<uint16_t *>(p.gv_out) + at;
+    uint32_t h[V];
+#pragma unroll
+    for (int t = 0; t < V; ++t) h[t] = sca_to_half(p, s[t]);
+    if (V == 4 && p.gv_vec) {
+        *reinterpret_cast<uint2 *>(o) =
+            make_uint2(h[0] | (h[V > 1 ? 1 : 0] << 16), h[V > 2 ? 2 : 0] | (h[V - 1] << 16));
+    } else {
+#pragma unroll
+        for (int t = 0; t < V; ++t) o[t] = (uint16_t)h[t];
+    }
+}
+
+// Element of the value gradient: channel c0 of the bin's pixel (0, 0).
+__device__ __forceinline__ uint64_t sca_bin_elem(const ScaParams &p, const ScaBin &q, int c0)
+{
+    return (uint64_t)q.bn * p.cam_elems +
+           ((uint64_t)p.level_start[q.l] + (uint64_t)q.py0 * p.level_w[q.l] + q.px0) * p.C +
+           (uint64_t)(q.head * p.D + c0);
+}
+
+// The first kSumWorkers wavefronts take the slices of the large bins in turn,
+// then each has one bin (and one of its channel slices).  Every XCD (blockIdx
+// mod 8) has its own share of the (batch element, camera, head) triples, so
+// that its L2 holds the output gradient of one camera's queries at a time.
+template <int SW>
+__global__ void __launch_bounds__(kScaWave, 4)
+sca_bin_sum(const ScaParams p)
+{
+    using S = ScaSum<SW>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int xcd = blockIdx.x % kScaXcds;
+    const int ncs = p.D / SW;   // channel slices
+    const bool full = p.misc[kMiscFull] != 0u;
+    const bool worker = blockIdx.x < (unsigned)kSumWorkers;
+    uint32_t k = (worker ? blockIdx.x : blockIdx.x - kSumWorkers) / kScaXcds;
+    uint32_t units = k + 1u;   // this wavefront's work: k, k + stride, ... below units
+    if (worker) units = full ? 0u : p.misc[kMiscXcd + xcd] * (uint32_t)ncs;
+    for (; k < units; k += kSumWorkers / kScaXcds) {
+        uint32_t gb, from = 0u, n, slot = 0u;
+        int cs;
+        if (worker) {
+            const uint32_t ks = k / (uint32_t)ncs;
+            cs = (int)(k - ks * (uint32_t)ncs);
+            const uint4 e = p.slices[(size_t)xcd * p.slice_cap + ks];
+            gb = e.x;
+            from = e.y;
+            slot = e.z;
+            n = min(p.bin_count[gb] - from, (uint32_t)kSumSlice);
+        } else {
+            const int bpu = p.bpc * ncs;
+            const int t = (int)k / bpu;
+            const int combo = xcd * p.combos_per_xcd + t;
+            const int BN = p.B * p.N;
+            if (combo >= BN * p.heads) return;
+            const int head = combo / BN;
+            const int u = ((int)k - t * bpu) / ncs;
+            cs = ((int)k - t * bpu) - u * ncs;
+            gb = (uint32_t)(((combo - head * BN) * p.heads + head) * p.bpc + u);
+            n = full ? 0u : p.bin_count[gb];
+            if (n > (uint32_t)kSumSlice) return;   // in slices
+        }
+        const ScaBin bin = sca_bin_of(p, gb);
+        sca_bin_records<SW>(p, smem, bin, cs * SW, p.recs + p.bin_start[gb] + from, n);
+        const v4f *out = reinterpret_cast<const v4f *>(smem);
+        if (worker) {
+            v4f *to = reinterpret_cast<v4f *>(p.partial + ((size_t)slot * ncs + cs) * S::kOut);
+            for (int i = threadIdx.x; i < S::kOut / 4; i += kScaWave) to[i] = out[i];
+        } else {
+            constexpr int Q4 = SW / 4;
+            const uint64_t at = sca_bin_elem(p, bin, cs * SW);
+            const int W = p.level_w[bin.l];
+            const int h = p.level_h[bin.l] - bin.py0, w = W - bin.px0;
+            const bool f32 = p.gv_dtype == FLASHBEV_F32 || full || p.misc[kMiscList];
+            for (int i = threadIdx.x; i < kBinPix * Q4; i += kScaWave) {
+                const int px = i / Q4, c = (i - px * Q4) * 4, y = px / kBinW, x = px - y * kBinW;
+                const v4f v = out[i];
+                if (y < h && x < w) {
+                    const float s[4] = {v[0], v[1], v[2], v[3]};
+                    sca_put<4>(p, at + (uint64_t)(y * W + x) * p.C + c, s, f32);
+                }
+            }
+        }
+        wave_lds_sync();
+    }
+}
+
+// Bins summed in slices: the slices' sums added up.
+template <int SW>
+__global__ void __launch_bounds__(256)
+sca_bin_join(const ScaParams p)
+{
+    constexpr int kOut = ScaSum<SW>::kOut;
+    if (p.misc[kMiscFull] != 0u) return;
+    const uint32_t ncs = (uint32_t)(p.D / SW);
+    const uint32_t nm = p.misc[kMiscMulti] * ncs * kBinH;   // a pixel row each
+    const bool f32 = p.gv_dtype == FLASHBEV_F32 || p.misc[kMiscList];
+    const int i = threadIdx.x;
+    const int x = i / SW, c = i - x * SW;
+    for (uint32_t k = blockIdx.x; k < nm; k += gridDim.x) {
+        const uint32_t ku = k / kBinH;
+        const int y = (int)(k - ku * kBinH);
+        const uint32_t km = ku / ncs, cs = ku - km * ncs;
+        const uint2 e = p.multi[km];
+        const uint32_t ns = (p.bin_count[e.x] + kSumSlice - 1) / kSumSlice;
+        const ScaBin bin = sca_bin_of(p, e.x);
+        const int W = p.level_w[bin.l];
+        if (x >= kBinW || bin.py0 + y >= p.level_h[bin.l] || bin.px0 + x >= W) continue;
+        const float *from = p.partial + ((size_t)e.y * ncs + cs) * kOut + y * kBinW * SW + i;
+        float s[1] = {0.0f};
+#pragma unroll 8
+        for (uint32_t q = 0; q < ns; ++q) s[0] += from[(size_t)q * ncs * kOut];
+        sca_put<1>(p, sca_bin_elem(p, bin, (int)cs * SW) + (uint64_t)(y * W + x) * p.C + c, s, f32);
+    }
+}
+
+// The float32 value gradient to its 16-bit storage type, where tiles were
+// left to the scatter form (sca_bin_sum has written it otherwise).
+__global__ void __launch_bounds__(256) sca_bin_round(const ScaParams p, uint64_t n)
+{
+    if (!p.misc[kMiscFull] && !p.misc[kMiscList]) return;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        static_cast<uint16_t *>(p.gv_out)[i] = sca_to_half(p, p.grad_value[i]);
+}
+
 __global__ void __launch_bounds__(256) sca_zero_fill(float *dst, uint64_t n)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -983,7 +1874,8 @@ struct ScaBufs {
     const float *lg = nullptr;
     const float *out = nullptr;
     const float *gout = nullptr;
-    const float *gvalue = nullptr;
+    const void *gvalue = nullptr;
+    int gv_dtype = FLASHBEV_F32;   // storage type of gvalue
     const float *goff = nullptr;
     const float *glg = nullptr;
 };
@@ -1119,15 +2011,17 @@ int make_sca_plan(const flashsca_value *v, const flashbev_bev_grid_spec *s,
                 if (v->N > 0 && !bf.l2i) return FLASHBEV_ERR_NULLPTR;
             }
             if (((uintptr_t)v->data % es) || ((uintptr_t)bf.l2i % 4) || ((uintptr_t)bf.gout % 4) ||
-                ((uintptr_t)bf.off % 8) || ((uintptr_t)bf.lg % 4) || ((uintptr_t)bf.gvalue % 4) ||
-                ((uintptr_t)bf.goff % 8) || ((uintptr_t)bf.glg % 4))
+                ((uintptr_t)bf.off % 8) || ((uintptr_t)bf.lg % 4) || ((uintptr_t)bf.goff % 8) || ((uintptr_t)bf.glg % 4))
                 return FLASHBEV_ERR_ALIGN;
             // every output is disjoint from every input and from the others
             const void *ins[5] = {v->data, bf.l2i, bf.off, bf.lg, bf.gout};
             const size_t insz[5] = {(size_t)value_bytes, (size_t)v->B * v->N * 64,
                                     (size_t)pts * 8, (size_t)pts * 4, ob};
             const void *outs[3] = {bf.gvalue, bf.goff, bf.glg};
-            const size_t outsz[3] = {(size_t)value_elems * 4, (size_t)pts * 8, (size_t)pts * 4};
+            const size_t gv_es = bf.gv_dtype == FLASHBEV_F32 ? 4 : 2;
+            if ((uintptr_t)bf.gvalue % gv_es) return FLASHBEV_ERR_ALIGN;
+            const size_t outsz[3] = {(size_t)value_elems * gv_es, (size_t)pts * 8,
+                                     (size_t)pts * 4};
             for (int a = 0; a < 3; ++a) {
                 for (int i = 0; i < 5; ++i)
                     if (sca_overlaps(outs[a], outsz[a], ins[i], insz[i])) return FLASHBEV_ERR_ALIAS;
@@ -1168,7 +2062,8 @@ int make_sca_plan(const flashsca_value *v, const flashbev_bev_grid_spec *s,
         // tp consecutive queries of one head
         nq_max = tp;
         if ((uint64_t)nq_max > Q) nq_max = (int)(Q > 0 ? Q : 1);
-        lay = sca_lds_layout(v->N, zb->Z, nq_max, waves, spw, LP, D, slot_stride, backward);
+        lay = sca_lds_layout(v->N, zb->Z, nq_max, waves, spw, LP, D, slot_stride,
+                             backward ? kScaScatter : kScaFwd);
         if (lay.total <= budget || waves == 1) break;
         waves >>= 1;
     }
@@ -1186,7 +2081,7 @@ int make_sca_plan(const flashsca_value *v, const flashbev_bev_grid_spec *s,
     p.logits = bf.lg;
     p.out = const_cast<float *>(bf.out);
     p.grad_out = bf.gout;
-    p.grad_value = const_cast<float *>(bf.gvalue);
+    p.grad_value = static_cast<float *>(const_cast<void *>(bf.gvalue));
     p.grad_offsets = const_cast<float *>(bf.goff);
     p.grad_logits = const_cast<float *>(bf.glg);
     p.cam_bytes = cam_bytes;
@@ -1265,6 +2160,175 @@ int make_sca_plan(const flashsca_value *v, const flashbev_bev_grid_spec *s,
     pl->empty = empty;
     pl->value_elems = value_elems;
     return FLASHBEV_OK;
+}
+
+// ---- binned backward: plan
+using ScaFn = const void *;
+
+template <int DT>
+ScaFn pick_points_lw(int lw, int lph)
+{
+    switch (lw) {
+    case 16: return lph == 8 ? (ScaFn)sca_bwd_points<DT, 16, 8> : (ScaFn)sca_bwd_points<DT, 16, 16>;
+    case 8: return lph == 8 ? (ScaFn)sca_bwd_points<DT, 8, 8> : (ScaFn)sca_bwd_points<DT, 8, 16>;
+    case 4: return lph == 8 ? (ScaFn)sca_bwd_points<DT, 4, 8> : (ScaFn)sca_bwd_points<DT, 4, 16>;
+    default:
+        if constexpr (DT == FLASHBEV_F32) return nullptr;
+        else
+            return lph == 8 ? (ScaFn)sca_bwd_points<DT, 2, 8> : (ScaFn)sca_bwd_points<DT, 2, 16>;
+    }
+}
+
+ScaFn pick_points(int dtype, int lw, int lph)
+{
+    if (dtype == FLASHBEV_F32) return pick_points_lw<FLASHBEV_F32>(lw, lph);
+    return dtype == FLASHBEV_F16 ? pick_points_lw<FLASHBEV_F16>(lw, lph)
+                                 : pick_points_lw<FLASHBEV_BF16>(lw, lph);
+}
+
+template <int DT>
+ScaFn pick_left_lw(int lw)
+{
+    switch (lw) {
+    case 16: return (ScaFn)sca_bwd_left<DT, 16>;
+    case 8: return (ScaFn)sca_bwd_left<DT, 8>;
+    case 4: return (ScaFn)sca_bwd_left<DT, 4>;
+    default:
+        if constexpr (DT == FLASHBEV_F32) return nullptr;
+        else return (ScaFn)sca_bwd_left<DT, 2>;
+    }
+}
+
+ScaFn pick_left(int dtype, int lw)
+{
+    if (dtype == FLASHBEV_F32) return pick_left_lw<FLASHBEV_F32>(lw);
+    return dtype == FLASHBEV_F16 ? pick_left_lw<FLASHBEV_F16>(lw) : pick_left_lw<FLASHBEV_BF16>(lw);
+}
+
+// LDS of the binned backward's count and point kernels, set in `p`.
+uint32_t binned_lds(ScaParams &p, int waves)
+{
+    const ScaLds lay = sca_lds_layout(p.N, p.Z, p.nq_max, waves, p.spw, p.LP, p.D, p.slot_stride,
+                                      kScaBinned);
+    p.lds_mat = lay.mat;
+    p.lds_lvl = lay.lvl;
+    p.lds_z = lay.z;
+    p.lds_ref = lay.ref;
+    p.lds_hit = lay.hit;
+    p.lds_tap = lay.tap;
+    p.lds_tab = lay.tab;
+    return lay.total;
+}
+
+struct ScaSumFn {
+    ScaFn fn, join;
+    size_t lds;
+};
+
+// channels summed at a time: whole head rows of 8, 16, 24 or 32, or halves
+int sum_width(int D) { return D == 48 ? 24 : D == 64 ? 32 : D; }
+
+ScaSumFn pick_sum(int D)
+{
+    switch (sum_width(D)) {
+    case 8: return {(ScaFn)sca_bin_sum<8>, (ScaFn)sca_bin_join<8>, ScaSum<8>::kBytes};
+    case 16: return {(ScaFn)sca_bin_sum<16>, (ScaFn)sca_bin_join<16>, ScaSum<16>::kBytes};
+    case 24: return {(ScaFn)sca_bin_sum<24>, (ScaFn)sca_bin_join<24>, ScaSum<24>::kBytes};
+    case 32: return {(ScaFn)sca_bin_sum<32>, (ScaFn)sca_bin_join<32>, ScaSum<32>::kBytes};
+    default: return {nullptr, nullptr, 0};
+    }
+}
+
+// Workspace of the binned backward: byte offsets of its parts.
+struct ScaWork {
+    uint64_t count, start, tile_n, list, tab, slices, multi, partial, recs, grad, total;
+    uint64_t tiles, rec_cap, slice_cap;
+};
+
+// Completes the scatter form's plan for the binned backward (level bins,
+// LDS) and lays its workspace out; FLASHBEV_ERR_UNSUPPORTED where it does not
+// serve: head rows that are not 8, 16, 24, 32, 48 or 64 channels or not on 8
+// or 16 lanes, and sizes beyond a record's or an index's bits.
+int plan_binned(const flashsca_value *v, ScaPlan *pl, ScaWork *w)
+{
+    ScaParams &p = pl->prm;
+    if (pl->empty || v->N < 1 || !pick_sum(p.D).fn || (p.lph != 8 && p.lph != 16))
+        return FLASHBEV_ERR_UNSUPPORTED;
+    if (p.Q >= (1 << kRecQBits) || (uint64_t)p.Q * p.C * 4u > kScaCamBytesMax)
+        return FLASHBEV_ERR_UNSUPPORTED;
+    uint64_t bins[FLASHSCA_LMAX], bpc = 0;
+    for (int l = 0; l < p.L; ++l) {
+        if (p.level_w[l] >= (1 << 15) || p.level_h[l] >= (1 << 15)) return FLASHBEV_ERR_UNSUPPORTED;
+        p.level_nbx[l] = (p.level_w[l] + kBinW - 1) / kBinW;
+        p.level_nby[l] = (p.level_h[l] + kBinH - 1) / kBinH;
+        bins[l] = (uint64_t)p.level_nbx[l] * p.level_nby[l];
+        bpc += bins[l];
+    }
+    const uint64_t combos = size_prod({(uint64_t)v->B, (uint64_t)v->N, (uint64_t)p.heads});
+    const uint64_t nb = size_prod({combos, bpc});
+    const uint64_t pts = size_prod({(uint64_t)v->B, (uint64_t)p.Q, (uint64_t)p.heads,
+                                    (uint64_t)p.LP});
+    w->tiles = size_prod({(uint64_t)v->B, (uint64_t)p.tiles_per_b});
+    if (nb > (1ull << 26) || pts > (1ull << 28) || w->tiles > (1ull << 22))
+        return FLASHBEV_ERR_UNSUPPORTED;
+    // Records: a point has one per hit camera and bin its footprint touches,
+    // about 1.2 on the six-camera ring and 1.6 with eight cameras; a call
+    // with more than twice its points takes the scatter form on the device.
+    w->rec_cap = 2 * pts;
+    // full slices of every record, and some
+    w->slice_cap = w->rec_cap / kSumSlice + 64;
+    int32_t at = 0;
+    for (int l = 0; l < p.L; ++l) {
+        p.level_bin0[l] = at;
+        at += (int32_t)bins[l];
+    }
+    p.bpc = (int32_t)bpc;
+    p.nbins = (uint32_t)nb;
+    p.rec_cap = (uint32_t)w->rec_cap;
+    p.slice_cap = (uint32_t)w->slice_cap;
+    p.combos_per_xcd = (int32_t)((combos + kScaXcds - 1) / kScaXcds);
+    uint64_t o = kMiscWords * 4;
+    auto take = [&o](uint64_t bytes) {
+        const uint64_t at0 = o;
+        o += (bytes + 255) & ~255ull;
+        return at0;
+    };
+    w->count = take(nb * 4);
+    w->start = take(nb * 4);
+    w->tile_n = take(w->tiles * 4);
+    w->list = take(w->tiles * 4);
+    w->tab = take(w->tiles * kTabMax * 8);
+    w->slices = take(kScaXcds * w->slice_cap * 16);
+    w->multi = take(w->slice_cap * 8);
+    w->partial = take(w->slice_cap * kBinPix * (uint64_t)p.D * 4);
+    w->recs = take(w->rec_cap * 16);
+    // float32 value gradient, used only where a 16-bit one cannot be binned
+    w->grad = take(v->dtype == FLASHBEV_F32 ? 0 : pl->value_elems * 4);
+    w->total = o;
+    return FLASHBEV_OK;
+}
+
+int launch_fn(ScaFn fn, ScaParams &p, uint64_t workgroups, int threads, size_t lds,
+              hipStream_t st)
+{
+    if (workgroups == 0) return FLASHBEV_OK;
+    if (workgroups > 0x7FFFFFFFull) return FLASHBEV_ERR_UNSUPPORTED;
+    if (lds > kScaLdsBudget &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return FLASHBEV_ERR_HIP;
+    void *args[] = {&p};
+    return hipLaunchKernel(fn, dim3((unsigned)workgroups), dim3(threads), args, lds, st) ==
+                   hipSuccess ? FLASHBEV_OK : FLASHBEV_ERR_HIP;
+}
+
+int launch_fill(float *dst, uint64_t n, hipStream_t st)
+{
+    uint64_t blocks = (n + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    void *args[] = {&dst, &n};
+    // the launch's own status (hipGetLastError could report an earlier call's)
+    return hipLaunchKernel(reinterpret_cast<const void *>(sca_zero_fill), dim3((unsigned)blocks),
+                           dim3(256), args, 0, st) == hipSuccess ? FLASHBEV_OK : FLASHBEV_ERR_HIP;
 }
 
 void write_info(const ScaPlan &pl, int64_t *workgroups, int32_t *threads, int32_t *lds,
@@ -1357,20 +2421,131 @@ extern "C" int flashsca_backward(const flashsca_value *value, const float *lidar
     if (rc) return rc;
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (grad_value && pl.value_elems > 0) {
-        uint64_t blocks = (pl.value_elems + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        // the launch's own status (hipGetLastError could report an earlier call's)
-        float *dst = grad_value;
-        uint64_t n = pl.value_elems;
-        void *fargs[] = {&dst, &n};
-        if (hipLaunchKernel(reinterpret_cast<const void *>(sca_zero_fill), dim3((unsigned)blocks),
-                            dim3(256), fargs, 0, st) != hipSuccess)
-            return FLASHBEV_ERR_HIP;
+        const int frc = launch_fill(grad_value, pl.value_elems, st);
+        if (frc) return frc;
     }
     if (pl.empty) return FLASHBEV_OK;
+    if (!grad_value && (pl.prm.lph == 8 || pl.prm.lph == 16)) {
+        // no rows to merge: the point kernel alone
+        const ScaFn points = pick_points(value->dtype, pl.lw, pl.prm.lph);
+        if (!points) return FLASHBEV_ERR_UNSUPPORTED;
+        const uint32_t lds = binned_lds(pl.prm, pl.threads / kScaWave);
+        return launch_fn(points, pl.prm, (uint64_t)pl.workgroups, pl.threads, lds, st);
+    }
     const ScaKernelFn fn = pick_sca(value->dtype, pl.lw, true);
     if (!fn) return FLASHBEV_ERR_UNSUPPORTED;
     return launch(fn, pl, st);
+}
+
+extern "C" int flashsca_backward_workspace_size(const flashsca_value *value,
+                                                const flashbev_bev_grid_spec *spec,
+                                                const flashbev_z_bins *anchors, int32_t P,
+                                                uint64_t *bytes)
+{
+    if (!bytes) return FLASHBEV_ERR_NULLPTR;
+    ScaPlan pl;
+    int rc = make_sca_plan(value, spec, anchors, P, ScaBufs{}, true, false, &pl);
+    if (rc) return rc;
+    ScaWork w;
+    rc = plan_binned(value, &pl, &w);
+    if (rc) return rc;
+    *bytes = w.total;
+    return FLASHBEV_OK;
+}
+
+extern "C" int flashsca_backward_ws(const flashsca_value *value, const float *lidar2img,
+                                    const flashbev_bev_grid_spec *spec,
+                                    const flashbev_z_bins *anchors, int32_t P,
+                                    const float *offsets, const float *logits,
+                                    const float *grad_out, void *grad_value,
+                                    int32_t grad_value_dtype, float *grad_offsets,
+                                    float *grad_logits, void *workspace,
+                                    uint64_t workspace_bytes, void *stream)
+{
+    if (!value) return FLASHBEV_ERR_NULLPTR;
+    if (grad_value_dtype != FLASHBEV_F32 && grad_value_dtype != value->dtype)
+        return FLASHBEV_ERR_DTYPE;
+    ScaBufs bf;
+    bf.l2i = lidar2img;
+    bf.off = offsets;
+    bf.lg = logits;
+    bf.gout = grad_out;
+    bf.gvalue = grad_value;
+    bf.gv_dtype = grad_value_dtype;
+    bf.goff = grad_offsets;
+    bf.glg = grad_logits;
+    ScaPlan pl;
+    int rc = make_sca_plan(value, spec, anchors, P, bf, true, true, &pl);
+    if (rc) return rc;
+    ScaWork w;
+    rc = plan_binned(value, &pl, &w);
+    if (rc) return rc;
+    if (!workspace) return FLASHBEV_ERR_NULLPTR;
+    if ((uintptr_t)workspace % 256) return FLASHBEV_ERR_ALIGN;
+    if (workspace_bytes < w.total) return FLASHBEV_ERR_SCRATCH;
+    const uint64_t pts = (uint64_t)pl.prm.B * pl.prm.Q * pl.prm.heads * pl.prm.LP;
+    const uint64_t rows = (uint64_t)pl.prm.B * pl.prm.Q * pl.prm.C * 4;
+    const uint64_t es = value->dtype == FLASHBEV_F32 ? 4 : 2;
+    const void *bufs[8] = {value->data, lidar2img, offsets, logits, grad_out, grad_value,
+                           grad_offsets, grad_logits};
+    const uint64_t sizes[8] = {pl.value_elems * es, (uint64_t)pl.prm.B * pl.prm.N * 64, pts * 8,
+                               pts * 4, rows,
+                               pl.value_elems * (grad_value_dtype == FLASHBEV_F32 ? 4 : 2),
+                               pts * 8, pts * 4};
+    for (int i = 0; i < 8; ++i)
+        if (sca_overlaps(workspace, w.total, bufs[i], sizes[i])) return FLASHBEV_ERR_ALIAS;
+
+    const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    char *ws = static_cast<char *>(workspace);
+    ScaParams left = pl.prm;   // the scatter form's LDS layout
+    left.misc = reinterpret_cast<uint32_t *>(ws);
+    left.bin_count = reinterpret_cast<uint32_t *>(ws + w.count);
+    left.bin_start = reinterpret_cast<uint32_t *>(ws + w.start);
+    left.tile_n = reinterpret_cast<uint32_t *>(ws + w.tile_n);
+    left.tile_list = reinterpret_cast<uint32_t *>(ws + w.list);
+    left.tile_tab = reinterpret_cast<uint2 *>(ws + w.tab);
+    left.slices = reinterpret_cast<uint4 *>(ws + w.slices);
+    left.multi = reinterpret_cast<uint2 *>(ws + w.multi);
+    left.partial = reinterpret_cast<float *>(ws + w.partial);
+    left.recs = grad_value ? reinterpret_cast<uint4 *>(ws + w.recs) : nullptr;
+    left.gv_out = grad_value;
+    left.gv_dtype = grad_value_dtype;
+    left.grad_value = grad_value_dtype == FLASHBEV_F32 ? static_cast<float *>(grad_value)
+                                                       : reinterpret_cast<float *>(ws + w.grad);
+    left.gv_vec = (uintptr_t)grad_value % (grad_value_dtype == FLASHBEV_F32 ? 16 : 8) == 0;
+    left.grad_offsets = nullptr;
+    left.grad_logits = nullptr;
+
+    ScaParams bp = left;
+    const uint32_t lds = binned_lds(bp, pl.threads / kScaWave);
+    bp.grad_offsets = grad_offsets;
+    bp.grad_logits = grad_logits;
+
+    const ScaFn points = pick_points(value->dtype, pl.lw, bp.lph);
+    const ScaFn scatter = pick_left(value->dtype, pl.lw);
+    if (!points || !scatter) return FLASHBEV_ERR_UNSUPPORTED;
+    const uint64_t tiles = (uint64_t)pl.workgroups;
+    if (grad_value) {
+        if ((rc = launch_fill(reinterpret_cast<float *>(ws), (w.start) / 4, st))) return rc;
+        if ((rc = launch_fn((ScaFn)sca_bin_count, bp, tiles, pl.threads, lds, st))) return rc;
+        if ((rc = launch_fn((ScaFn)sca_bin_alloc, bp, (bp.nbins + 255) / 256, 256, 0, st))) return rc;
+    }
+    if ((rc = launch_fn(points, bp, tiles, pl.threads, lds, st))) return rc;
+    if (!grad_value) return FLASHBEV_OK;
+    const ScaSumFn sum = pick_sum(bp.D);
+    if ((rc = launch_fn(sum.fn, bp,
+                        kSumWorkers + (uint64_t)bp.combos_per_xcd * bp.bpc * (bp.D / sum_width(bp.D)) *
+                                          kScaXcds,
+                        kScaWave, sum.lds, st)))
+        return rc;
+    if ((rc = launch_fn(sum.join, bp, w.slice_cap < 512 ? w.slice_cap * kBinH : 4096, 256, 0, st)))
+        return rc;
+    if ((rc = launch_fn(scatter, left, tiles < 512 ? tiles : 512, pl.threads, pl.lds, st))) return rc;
+    if (grad_value_dtype == FLASHBEV_F32) return FLASHBEV_OK;
+    uint64_t n = pl.value_elems;
+    void *args[] = {&left, &n};
+    return hipLaunchKernel(reinterpret_cast<const void *>(sca_bin_round), dim3(2048), dim3(256), args,
+                           0, st) == hipSuccess ? FLASHBEV_OK : FLASHBEV_ERR_HIP;
 }
 
 #ifdef FLASHBEV_PHASE_CLOCK
