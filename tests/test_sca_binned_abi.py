@@ -75,9 +75,9 @@ def test_workspace_size_and_checks():
 def test_python_method_argument():
     v, g, zb, _z = structs()
     with pytest.raises(ValueError):
-        fb._sca_workspace_bytes(v, g, zb, 8, "sorted", 1, True)
+        fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "sorted", 1, True)
     big = fb.SCA_BINNED_MIN_POINTS
-    assert fb._sca_workspace_bytes(v, g, zb, 8, "auto", big - 1, True) == -1
-    assert fb._sca_workspace_bytes(v, g, zb, 8, "auto", big, None) == -1
-    assert fb._sca_workspace_bytes(v, g, zb, 8, "auto", big, True) == size()[1]
-    assert fb._sca_workspace_bytes(v, g, zb, 8, "scatter", big, True) == -1
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "auto", big - 1, True) == -1
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "auto", big, None) == -1
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "auto", big, True) == size()[1]
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "scatter", big, True) == -1
