@@ -224,6 +224,18 @@ int flashbev_sample_vt_backward_ws(const flashbev_features *features, const floa
                                    uint64_t workspace_bytes, void *stream);
 
 /*
+ * flashbev_sample_vt_backward_ws with the gradient stored as `grad_dtype`:
+ * FLASHBEV_F32, or the features' dtype (the float32 sum of each element
+ * rounded once to nearest even), aligned to it.  FLASHBEV_ERR_DTYPE for any
+ * other type.
+ */
+int flashbev_sample_vt_backward_ws_as(const flashbev_features *features, const float *lidar2img,
+                                      const flashbev_bev_grid_spec *spec,
+                                      const flashbev_z_bins *z_bins, const float *grad_out,
+                                      void *grad_features, int32_t grad_dtype, void *workspace,
+                                      uint64_t workspace_bytes, void *stream);
+
+/*
  * flashbev_sample_vt_backward_ws without a caller workspace and without any
  * allocation, for callers that cannot call hipMalloc: work captured into a
  * HIP graph, tight serving loops, harnesses that forbid allocation.  The

@@ -441,14 +441,25 @@ def sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_hw: Tuple
 
     Returns ``grad_features`` (float32, channel-last).  Asynchronous.
     """
+    return _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shape,
+                               features_dtype, grad_features, reduce, stream, method, workspace,
+                               None)
+
+
+def _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shape, features_dtype,
+                        grad_features, reduce, stream, method, workspace, grad_dtype):
+    """sample_vt_backward; ``grad_dtype`` (a torch dtype) asks for the gradient
+    in the features' type, rounded once (by the gather form as it writes)."""
     import torch
 
     if method not in BACKWARD_METHODS:
         raise ValueError(f"method must be one of {BACKWARD_METHODS}")
     B, N, H, W, C = _check_backward(grad_out, lidar2img, grid, features_shape)
-    if grad_features is None:
+    convert = grad_dtype is not None and grad_dtype != torch.float32
+    if grad_features is None and not convert:
         grad_features = torch.empty((B, N, H, W, C), dtype=torch.float32, device=grad_out.device)
-    _check_out(grad_features, (B, N, H, W, C), "grad_features")
+    if grad_features is not None:
+        _check_out(grad_features, (B, N, H, W, C), "grad_features")
     features_dtype = _dtype_name(features_dtype)
     z = _z_array(z_bins)
     f, g, zb = _packed((B, N, H, W, C), DTYPE_CODES[features_dtype], 0, img_hw, grid, z, reduce)
@@ -464,20 +475,24 @@ def sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_hw: Tuple
                 workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=grad_out.device)
             elif not workspace.is_cuda or workspace.numel() * workspace.element_size() < need:
                 raise ValueError(f"workspace must be a device tensor of at least {need} bytes")
-            call = _packed_call("flashbev_sample_vt_backward_ws", "PPPPPPPQP")
+            if convert:
+                grad_features = torch.empty((B, N, H, W, C), dtype=grad_dtype, device=grad_out.device)
+            call = _packed_call("flashbev_sample_vt_backward_ws_as", "PPPPPPiPQP")
             with _on_device(dev):
                 rc = call(f, lidar2img.data_ptr(), g, zb, grad_out.data_ptr(),
-                          grad_features.data_ptr(), workspace.data_ptr(),
-                          workspace.numel() * workspace.element_size(), s)
+                          grad_features.data_ptr(), _dtype_code(grad_features),
+                          workspace.data_ptr(), workspace.numel() * workspace.element_size(), s)
             if rc != 0:
                 raise FlashBevError(rc, "flashbev_sample_vt_backward_ws")
             return grad_features
+    if convert:
+        grad_features = torch.empty((B, N, H, W, C), dtype=torch.float32, device=grad_out.device)
     call = _packed_call("flashbev_sample_vt_backward", "PPPPPPP")
     with _on_device(dev):
         rc = call(f, lidar2img.data_ptr(), g, zb, grad_out.data_ptr(), grad_features.data_ptr(), s)
     if rc != 0:
         raise FlashBevError(rc, "flashbev_sample_vt_backward")
-    return grad_features
+    return grad_features.to(grad_dtype) if convert else grad_features
 
 
 def sample_vt_backward_raw(shape, dtype: str, lidar2img_ptr: int, z_bins, grid: BevGrid,
@@ -1037,10 +1052,9 @@ def _autograd_functions():
             shape, dtype, z_bins, grid, img_hw, reduce, method = ctx.meta
             g = None
             if ctx.needs_input_grad[0]:
-                g = sample_vt_backward(grad_out.float().contiguous(), l2i, z_bins, grid, img_hw,
-                                       shape, _dtype_name(dtype), reduce=reduce, method=method)
-                if g.dtype != dtype:
-                    g = g.to(dtype)
+                g = _sample_vt_backward(grad_out.float().contiguous(), l2i, z_bins, grid, img_hw,
+                                        shape, _dtype_name(dtype), None, reduce, None, method, None,
+                                        dtype)
             return g, None, None, None, None, None, None
 
     class _SCA(torch.autograd.Function):

@@ -1464,7 +1464,8 @@ sample_vt_bwd(const BwdParams p)
 struct BwdGatherParams {
     const float *l2i;
     const float *gout;       // [B, C, X, Y]
-    float *gfeat;            // [B, N, H, W, C]
+    float *gfeat;            // [B, N, H, W, C], of gfeat_dtype
+    int32_t gfeat_dtype;     // float32, or a 16-bit type the float32 sums are rounded to once
     float *gt;               // workspace: [B, X Y, C]
     uint8_t *den;            // workspace: [B, X Y, Z]
     uint32_t gt_bytes;       // bytes of gt (buffer size for the descriptor)
@@ -1493,6 +1494,12 @@ struct BwdGatherParams {
     uint32_t lds_wave;       // LDS bytes per wavefront
     float z[FLASHBEV_ZMAX];
 };
+
+// float32 to half or bfloat16 bits, rounded to nearest even
+__device__ __forceinline__ uint16_t to_half(bool half, float v)
+{
+    return half ? __builtin_bit_cast(uint16_t, (_Float16)v) : __builtin_bit_cast(uint16_t, (__bf16)v);
+}
 
 constexpr int kPrepCells = 64;      // cells per prep workgroup
 constexpr int kGatherRec = 128;     // records per pixel list (two candidate chunks)
@@ -2026,17 +2033,29 @@ sample_vt_bwd_gather(const BwdGatherParams p)
 
     // single write of the group's gradient rows (NHWC, contiguous)
     if (g_active) {
-        float *dst = p.gfeat + ((((size_t)b * p.N + n) * p.H + py) * p.W + px0 + m_g) * p.C;
-        float *dst1 = dst + (size_t)p.W * p.C;   // row py + 1
+        const size_t at = ((((size_t)b * p.N + n) * p.H + py) * p.W + px0 + m_g) * p.C;
+        const size_t next = (size_t)p.W * p.C;   // row py + 1
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
             const int vi = slot + L * v;
             if (VPL == 1 || vi < p.nvec) {
+                const size_t e0 = at + (size_t)vi * EPV;
+                if (p.gfeat_dtype == FLASHBEV_F32) {
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) dst[vi * EPV + e] = acc[v][e];
-                if (ROWS == 2 && nrows == 2) {
+                    for (int e = 0; e < EPV; ++e) p.gfeat[e0 + e] = acc[v][e];
+                    if (ROWS == 2 && nrows == 2) {
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) dst1[vi * EPV + e] = acc1[v][e];
+                        for (int e = 0; e < EPV; ++e) p.gfeat[e0 + next + e] = acc1[v][e];
+                    }
+                } else {
+                    uint16_t *o = reinterpret_cast<uint16_t *>(p.gfeat) + e0;
+                    const bool half = p.gfeat_dtype == FLASHBEV_F16;
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) o[e] = to_half(half, acc[v][e]);
+                    if (ROWS == 2 && nrows == 2) {
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) o[next + e] = to_half(half, acc1[v][e]);
+                    }
                 }
             }
         }
@@ -2378,7 +2397,7 @@ BwdKernelFn pick_bwd(int kpl, bool tiled, bool wide)
 // All argument checks; `need_data` requires the device pointers.
 int make_bwd_plan(const flashbev_features *f, const float *l2i, const flashbev_bev_grid_spec *s,
                   const flashbev_z_bins *zb, const float *gout, const float *gfeat, bool need_data,
-                  BwdPlan *pl)
+                  BwdPlan *pl, int gfeat_dtype = FLASHBEV_F32)
 {
     if (!f || !s || !zb) return FLASHBEV_ERR_NULLPTR;
     if (f->dtype != FLASHBEV_F32 && f->dtype != FLASHBEV_F16 && f->dtype != FLASHBEV_BF16)
@@ -2405,13 +2424,13 @@ int make_bwd_plan(const flashbev_features *f, const float *l2i, const flashbev_b
     if (zb->Z > 0 && !zb->z) return FLASHBEV_ERR_NULLPTR;
     if (need_data && gelems > 0) {
         if (!gfeat) return FLASHBEV_ERR_NULLPTR;
-        if ((uintptr_t)gfeat % 4) return FLASHBEV_ERR_ALIGN;
+        if ((uintptr_t)gfeat % (gfeat_dtype == FLASHBEV_F32 ? 4 : 2)) return FLASHBEV_ERR_ALIGN;
     }
     const bool scatter = gelems > 0 && out_elems > 0 && zb->Z > 0;
     if (need_data && scatter) {
         if (!gout || !l2i) return FLASHBEV_ERR_NULLPTR;
         if (((uintptr_t)gout % 4) || ((uintptr_t)l2i % 4)) return FLASHBEV_ERR_ALIGN;
-        const size_t gb = gelems * 4;
+        const size_t gb = gelems * (gfeat_dtype == FLASHBEV_F32 ? 4 : 2);
         if (overlaps(gfeat, gb, gout, out_elems * 4) ||
             overlaps(gfeat, gb, l2i, (size_t)f->B * f->N * 64))
             return FLASHBEV_ERR_ALIAS;
@@ -2636,12 +2655,14 @@ uint64_t align256(uint64_t v) { return (v + 255u) & ~(uint64_t)255u; }
 int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
                          const flashbev_bev_grid_spec *s, const flashbev_z_bins *zb,
                          const float *gout, const float *gfeat, const void *ws, uint64_t ws_bytes,
-                         bool need_data, BwdGatherPlan *pl, bool check_ws = true)
+                         bool need_data, BwdGatherPlan *pl, bool check_ws = true,
+                         int gfeat_dtype = FLASHBEV_F32)
 {
     // the shape, value, pointer and alias checks of the scatter-form backward
     BwdPlan bp;
-    const int rc = make_bwd_plan(f, l2i, s, zb, gout, gfeat, need_data, &bp);
+    const int rc = make_bwd_plan(f, l2i, s, zb, gout, gfeat, need_data, &bp, gfeat_dtype);
     if (rc) return rc;
+    const uint64_t gfeat_es = gfeat_dtype == FLASHBEV_F32 ? 4 : 2;
     const uint64_t XY = (uint64_t)s->X * (uint64_t)s->Y;
     const uint64_t row = (uint64_t)f->C * 4u;   // float32 gradient rows
     if (row > FLASHBEV_ROW_BYTES_MAX) return FLASHBEV_ERR_UNSUPPORTED;
@@ -2658,7 +2679,7 @@ int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
         if ((uintptr_t)ws % 256u) return FLASHBEV_ERR_ALIGN;
         if (ws_bytes < need) return FLASHBEV_ERR_VALUE;
         // the workspace overlaps none of the call's buffers
-        if (overlaps(ws, need, gfeat, gelems * 4) ||
+        if (overlaps(ws, need, gfeat, gelems * gfeat_es) ||
             overlaps(ws, need, gout, size_prod({(uint64_t)f->B, (uint64_t)f->C, XY}) * 4) ||
             overlaps(ws, need, l2i, (size_t)f->B * f->N * 64))
             return FLASHBEV_ERR_ALIAS;
@@ -2682,6 +2703,7 @@ int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
     p.l2i = l2i;
     p.gout = gout;
     p.gfeat = const_cast<float *>(gfeat);
+    p.gfeat_dtype = gfeat_dtype;
     p.gt = reinterpret_cast<float *>(const_cast<void *>(ws));
     p.den = ws ? reinterpret_cast<uint8_t *>(const_cast<void *>(ws)) + align256(gt_bytes) : nullptr;
     p.gt_bytes = (uint32_t)gt_bytes;
@@ -2981,6 +3003,24 @@ extern "C" int flashbev_sample_vt_backward_ws(const flashbev_features *features,
     BwdGatherPlan pl;
     const int rc = make_bwd_gather_plan(features, lidar2img, spec, z_bins, grad_out, grad_features,
                                         workspace, workspace_bytes, true, &pl);
+    if (rc) return rc;
+    return launch_bwd_gather(pl, reinterpret_cast<hipStream_t>(stream));
+}
+
+extern "C" int flashbev_sample_vt_backward_ws_as(const flashbev_features *features,
+                                                 const float *lidar2img,
+                                                 const flashbev_bev_grid_spec *spec,
+                                                 const flashbev_z_bins *z_bins,
+                                                 const float *grad_out, void *grad_features,
+                                                 int32_t grad_dtype, void *workspace,
+                                                 uint64_t workspace_bytes, void *stream)
+{
+    if (!features) return FLASHBEV_ERR_NULLPTR;
+    if (grad_dtype != FLASHBEV_F32 && grad_dtype != features->dtype) return FLASHBEV_ERR_DTYPE;
+    BwdGatherPlan pl;
+    const int rc = make_bwd_gather_plan(features, lidar2img, spec, z_bins, grad_out,
+                                        static_cast<const float *>(grad_features), workspace,
+                                        workspace_bytes, true, &pl, true, grad_dtype);
     if (rc) return rc;
     return launch_bwd_gather(pl, reinterpret_cast<hipStream_t>(stream));
 }

@@ -37,8 +37,12 @@ def test_packed_structures_match_the_ctypes_ones():
 def test_values_past_the_c_types_take_the_structures():
     z = np.zeros(2, np.float32)
     g = fb.BevGrid(-1e300, 1.0, 4, 0.0, 1.0, 4)          # float32 overflow: infinity there
+    # float32 overflow is an infinity either way
     a = fb._packed((1, 1, 2, 2, 4), 0, 0, (4, 4), g, z, "mean")
-    assert not isinstance(a[1], bytes)
+    assert a[1] == raw(fb._structs((1, 1, 2, 2, 4), 0, 0, (4, 4), g, z, "mean")[1])
+    # an integer past 32 bits wraps in the structure
+    a = fb._packed((1, 1, 2, 2, (1 << 32) + 4), 0, 0, (4, 4), g, z, "mean")
+    assert not isinstance(a[0], bytes)
     assert fb._packed_call("flashbev_sample_vt", "PPPPPP")(a[0], 0, a[1], a[2], 0, 0) == \
         fb.STATUS["ERR_VALUE"]
     with pytest.raises(ValueError):
@@ -51,3 +55,21 @@ def test_empty_heights_have_an_address():
     assert isinstance(fb._address(np.zeros(0, np.float32)), int)
     assert fb._packed_call("flashbev_sample_vt", "PPPPPP")(None, 0, None, None, 0, 0) == \
         fb.STATUS["ERR_NULLPTR"]
+
+
+def test_gradient_types_of_the_gather_form():
+    import ctypes
+    z = np.zeros(2, np.float32)
+    f, g, zb = fb._packed((1, 1, 2, 2, 4), fb.DTYPE_CODES["bf16"], 0, (4, 4),
+                          fb.BevGrid(-1, 1, 4, -1, 1, 4), z, "mean")
+    call = fb._packed_call("flashbev_sample_vt_backward_ws_as", "PPPPPPiPQP")
+    base = 0x7F0000000000
+    args = lambda grad, code, ws: (f, base, g, zb, base + 4096, grad, code, ws, 1 << 20, 0)
+    S = fb.STATUS
+    assert call(*args(base + 8192, fb.DTYPE_CODES["f16"], base + (1 << 24))) == S["ERR_DTYPE"]
+    assert call(*args(base + 8193, fb.DTYPE_CODES["bf16"], base + (1 << 24))) == S["ERR_ALIGN"]
+    assert call(*args(base + 8194, fb.DTYPE_CODES["f32"], base + (1 << 24))) == S["ERR_ALIGN"]
+    # a 16-bit gradient of 32 bytes right before the output gradient is no overlap
+    assert call(*args(base + 4096 - 32, fb.DTYPE_CODES["bf16"], base + (1 << 24) + 1)) == S["ERR_ALIGN"]
+    assert call(*args(base + 4096 - 30, fb.DTYPE_CODES["bf16"], base + (1 << 24))) == S["ERR_ALIAS"]
+    assert call(None, *args(0, 0, 0)[1:]) == S["ERR_NULLPTR"]
