@@ -393,6 +393,8 @@ sample_vt_fwd(const Params p)
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.feat), (short)0,
                                           (int)p.feat_bytes, 0x00020000);
 
+    // the last vector of a row ends with it and may overlap the one before
+    const uint32_t last_vec = p.row_bytes - LW;
     float4 *wl = s_w + (size_t)wave * cpw * RS;
     uint32_t *ol = s_off + (size_t)wave * cpw * RS;
     uint32_t *cl = reinterpret_cast<uint32_t *>(smem + p.lds_cl) + wave * kWave;  // visible cameras
@@ -436,7 +438,7 @@ sample_vt_fwd(const Params p)
                         Raw<LW> t[kUnroll][4];
 #pragma unroll
                         for (int u = 0; u < kUnroll; ++u) {
-                            const uint32_t vo = base[u] + (uint32_t)vi * LW;
+                            const uint32_t vo = base[u] + min((uint32_t)vi * LW, last_vec);
                             t[u][0] = load_vec<LW>(rsrc, vo, 0u);
                             t[u][1] = load_vec<LW>(rsrc, vo, p.step_x);
                             t[u][2] = load_vec<LW>(rsrc, vo, p.step_y);
@@ -813,7 +815,7 @@ sample_vt_fwd(const Params p)
                 if (VPL == 1 || vi < p.nvec) {
 #pragma unroll
                     for (int e = 0; e < EPV; ++e)
-                        s_tile[(vi * EPV + e) * p.otile_ld + col] = acc[v][e];
+                        s_tile[(min(vi * EPV, p.C - EPV) + e) * p.otile_ld + col] = acc[v][e];
                 }
             }
         }
@@ -1726,7 +1728,7 @@ sample_vt_bwd_gather(const BwdGatherParams p)
                         Raw<LW> t[kGatherUnroll];
 #pragma unroll
                         for (int u = 0; u < kGatherUnroll; ++u)
-                            t[u] = load_vec<LW>(rsrc, base[u] + (uint32_t)vi * LW, 0u);
+                            t[u] = load_vec<LW>(rsrc, base[u] + min((uint32_t)vi * LW, p.row_bytes - LW), 0u);
 #pragma unroll
                         for (int u = 0; u < kGatherUnroll; ++u)
 #pragma unroll
@@ -2039,7 +2041,7 @@ sample_vt_bwd_gather(const BwdGatherParams p)
         for (int v = 0; v < VPL; ++v) {
             const int vi = slot + L * v;
             if (VPL == 1 || vi < p.nvec) {
-                const size_t e0 = at + (size_t)vi * EPV;
+                const size_t e0 = at + (size_t)min(vi * EPV, p.C - EPV);
                 if (p.gfeat_dtype == FLASHBEV_F32) {
 #pragma unroll
                     for (int e = 0; e < EPV; ++e) p.gfeat[e0 + e] = acc[v][e];
@@ -2186,10 +2188,19 @@ int make_plan(const flashbev_features *f, const float *l2i, const flashbev_bev_g
     }
 
     // vector width: the widest of 16/8/4/2 bytes dividing the row and the
-    // base address
+    // base address, or 16 (below)
     int lw = 16;
     while (lw > es && ((row % lw) != 0 || (((uintptr_t)f->data) % lw) != 0)) lw >>= 1;
-    const int nvec = (int)(row / lw);
+    // Rows of whole dwords take 16-byte vectors all the same, from 128 bytes
+    // on: the loads need dword alignment only, and a row's last vector is
+    // moved back to end with it (both lanes then hold the shared channels and
+    // store the same sums).  Narrower rows would leave lanes idle.  Measured
+    // on MI355X at 200 x 200 x 8, six cameras, before / with: C = 99 float32
+    // 49.6 / 34.4 us, 130 70 / 42, 255 92 / 57, 33 24.9 / 17.0; bfloat16
+    // C = 250 51 / 40, 66 28.2 / 21.7, but 34 (68 bytes) 18.0 / 18.9 and 12
+    // 15.0 / 17.4.
+    if (lw < 16 && row >= 128 && row % 4 == 0 && ((uintptr_t)f->data) % 4 == 0) lw = 16;
+    const int nvec = (int)((row + lw - 1) / lw);
     int vpl = 1;
     while (vpl < 4 && (nvec + vpl - 1) / vpl > kWave) vpl <<= 1;
     // wide rows: give a lane several vectors so that a wavefront covers at
@@ -2689,7 +2700,12 @@ int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
     // 1 KiB rows on), as the forward lays out its feature rows
     int lw = 16;
     while (lw > 4 && (row % lw) != 0) lw >>= 1;
-    const int nvec = (int)(row / lw);
+    // rows of 64 channels or more take 16-byte vectors all the same, the last
+    // one moved back to end with the row, as in the forward (measured on
+    // MI355X at 200 x 200 x 8: C = 66 84 -> 66 us, 99 114 -> 70, 201 136 ->
+    // 115; narrower rows then put too many pixels in a group: C = 34 65 -> 83)
+    if (row >= 256) lw = 16;
+    const int nvec = (int)((row + lw - 1) / lw);
     int vpl = 1;
     while (vpl < 4 && (nvec + vpl - 1) / vpl > kWave) vpl <<= 1;
     const int min_cpw = row >= 1024 ? 4 : 2;
