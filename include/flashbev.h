@@ -260,6 +260,15 @@ int flashbev_sample_vt_backward_noalloc(const flashbev_features *features,
                                         const flashbev_z_bins *z_bins, const float *grad_out,
                                         float *grad_features, void *stream);
 
+/* Workspace bytes with which flashbev_sample_vt_backward_ws and _ws_as run
+ * fastest: on small maps the minimum below and room for partial sums, with
+ * which several wavefronts share a pixel group's heights (their sums are added
+ * in a fixed order, which is not the order of a smaller workspace's call).
+ * The room must overlap no other buffer. */
+int flashbev_backward_workspace_best(const flashbev_features *features,
+                                     const flashbev_bev_grid_spec *spec,
+                                     const flashbev_z_bins *z_bins, uint64_t *bytes);
+
 /*
  * Workspace bytes flashbev_sample_vt_backward_ws needs for these arguments
  * (written to *bytes; a multiple of 256).  Same shape checks, no device

@@ -472,7 +472,10 @@ def _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shap
             method = "scatter"
         else:
             if workspace is None:
-                workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=grad_out.device)
+                best = ctypes.c_uint64()
+                _packed_call("flashbev_backward_workspace_best", "PPPP")(f, g, zb, ctypes.byref(best))
+                workspace = torch.empty(max(need, best.value, 1), dtype=torch.uint8,
+                                        device=grad_out.device)
             elif not workspace.is_cuda or workspace.numel() * workspace.element_size() < need:
                 raise ValueError(f"workspace must be a device tensor of at least {need} bytes")
             if convert:
@@ -680,7 +683,10 @@ def prepare_sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_h
     if method == "gather":
         need = backward_workspace_size((B, N, H, W, C), features_dtype, z, grid, img_hw, reduce)
         if need >= 0:
-            ws = torch.empty(max(need, 1), dtype=torch.uint8, device=grad_out.device)
+            best = ctypes.c_uint64()
+            _packed_call("flashbev_backward_workspace_best", "PPPP")(
+                ctypes.byref(f), ctypes.byref(g), ctypes.byref(zb), ctypes.byref(best))
+            ws = torch.empty(max(need, best.value, 1), dtype=torch.uint8, device=grad_out.device)
             args = (ctypes.byref(f), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
                     ctypes.byref(zb), ctypes.c_void_p(grad_out.data_ptr()),
                     ctypes.c_void_p(grad_features.data_ptr()), ctypes.c_void_p(ws.data_ptr()),

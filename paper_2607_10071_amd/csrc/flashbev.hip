@@ -1470,6 +1470,9 @@ struct BwdGatherParams {
     int32_t gfeat_dtype;     // float32, or a 16-bit type the float32 sums are rounded to once
     float *gt;               // workspace: [B, X Y, C]
     uint8_t *den;            // workspace: [B, X Y, Z]
+    float *part;             // workspace: [splits, B, N, H, W, C] sums, where splits > 1
+    uint64_t elems;          // B N H W C
+    int32_t splits;          // wavefronts that share a pixel group's heights
     uint32_t gt_bytes;       // bytes of gt (buffer size for the descriptor)
     int32_t B, N, H, W, C, X, Y, Z;
     int32_t XY;
@@ -1804,8 +1807,11 @@ sample_vt_bwd_gather(const BwdGatherParams p)
             pairt[lane * 2 + 1] = be != 0.0 ? 1.0 / be : 0.0;
         }
         wave_lds_sync();
-        for (int k0 = 0; k0 < p.Z; k0 += kHeightBatch) {
-            const int nb = (p.Z - k0) < kHeightBatch ? (p.Z - k0) : kHeightBatch;
+        // this wavefront's share of the heights
+        const int k_end = (int)((blockIdx.y + 1u) * (uint32_t)p.Z / (uint32_t)p.splits);
+        for (int k0 = (int)(blockIdx.y * (uint32_t)p.Z / (uint32_t)p.splits); k0 < k_end;
+             k0 += kHeightBatch) {
+            const int nb = (k_end - k0) < kHeightBatch ? (k_end - k0) : kHeightBatch;
             // lanes over the batch's heights: each height's offsets gam_q
             // and the range of grid rows that can hold a candidate
             float zv = 0.0f;
@@ -2042,12 +2048,13 @@ sample_vt_bwd_gather(const BwdGatherParams p)
             const int vi = slot + L * v;
             if (VPL == 1 || vi < p.nvec) {
                 const size_t e0 = at + (size_t)min(vi * EPV, p.C - EPV);
-                if (p.gfeat_dtype == FLASHBEV_F32) {
+                if (p.splits > 1 || p.gfeat_dtype == FLASHBEV_F32) {
+                    float *o = p.splits > 1 ? p.part + blockIdx.y * p.elems : p.gfeat;
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) p.gfeat[e0 + e] = acc[v][e];
+                    for (int e = 0; e < EPV; ++e) o[e0 + e] = acc[v][e];
                     if (ROWS == 2 && nrows == 2) {
 #pragma unroll
-                        for (int e = 0; e < EPV; ++e) p.gfeat[e0 + next + e] = acc1[v][e];
+                        for (int e = 0; e < EPV; ++e) o[e0 + next + e] = acc1[v][e];
                     }
                 } else {
                     uint16_t *o = reinterpret_cast<uint16_t *>(p.gfeat) + e0;
@@ -2061,6 +2068,18 @@ sample_vt_bwd_gather(const BwdGatherParams p)
                 }
             }
         }
+    }
+}
+
+// The shares' sums added up in order, and written as the caller takes them.
+__global__ void __launch_bounds__(256) sample_vt_bwd_join(const BwdGatherParams p)
+{
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.elems; i += stride) {
+        float s = p.part[i];
+        for (int k = 1; k < p.splits; ++k) s += p.part[k * p.elems + i];
+        if (p.gfeat_dtype == FLASHBEV_F32) p.gfeat[i] = s;
+        else reinterpret_cast<uint16_t *>(p.gfeat)[i] = to_half(p.gfeat_dtype == FLASHBEV_F16, s);
     }
 }
 
@@ -2628,9 +2647,13 @@ struct BwdGatherPlan {
     int lw, vpl;
     int rows;              // feature-map rows per gather group
     uint64_t ws_bytes;     // workspace bytes needed
+    uint64_t ws_best;      // with room for the shared heights' sums
 };
 
 constexpr int kGatherWaves = 1;   // gather: wavefronts per workgroup (one: finest balance)
+constexpr int64_t kSplitGroups = 16384;   // heights are shared up to this many wavefronts
+constexpr uint64_t kSplitVoxels = 200;    // voxels per group from which they are
+constexpr int kSplitMax = 8;
 
 using BwdGatherFn = void (*)(const BwdGatherParams);
 
@@ -2667,7 +2690,7 @@ int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
                          const flashbev_bev_grid_spec *s, const flashbev_z_bins *zb,
                          const float *gout, const float *gfeat, const void *ws, uint64_t ws_bytes,
                          bool need_data, BwdGatherPlan *pl, bool check_ws = true,
-                         int gfeat_dtype = FLASHBEV_F32)
+                         int gfeat_dtype = FLASHBEV_F32, bool split = true)
 {
     // the shape, value, pointer and alias checks of the scatter-form backward
     BwdPlan bp;
@@ -2760,6 +2783,38 @@ int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
                          kGatherTail);
     for (int k = 0; k < zb->Z; ++k) p.z[k] = zb->z[k];
 
+    // Few pixel groups of many samples each (small maps under a large grid)
+    // leave most of the chip idle: their heights are then shared by several
+    // wavefronts each, whose sums a second kernel adds in order, where the
+    // workspace has room for them.  Taken from 200 voxels per group on (each
+    // is seen by about one camera), where at least three shares fit 16384
+    // wavefronts.  Measured on MI355X, one wavefront per group / shared us:
+    // 16 x 44 maps under 200 x 200 x 8, C = 32 230 / 109, 80 121 / 85, 128
+    // 163 / 82, 256 423 / 190; 17 x 39 under 343 x 422 x 12 1690 / 551; 28 x 50
+    // under 300 x 300 x 16 469 / 335; but with fewer voxels per group 28 x 50
+    // under 200 x 200 x 8 (146) 112 / 125, 32 x 88 with C = 32 (151) 91 / 127.
+    p.elems = gelems;
+    p.splits = 1;
+    p.part = nullptr;
+    pl->ws_best = need;
+    const uint64_t voxels = size_prod({(uint64_t)f->B, XY, (uint64_t)zb->Z});
+    if (gelems > 0 && zb->Z > 1 && p.groups * 3 <= kSplitGroups &&
+        voxels >= (uint64_t)p.groups * kSplitVoxels) {
+        int64_t sp = kSplitGroups / p.groups;
+        if (sp > kSplitMax) sp = kSplitMax;
+        if (sp > zb->Z) sp = zb->Z;
+        pl->ws_best = need + align256((uint64_t)sp * gelems * 4u);
+        if (ws && split && ws_bytes >= pl->ws_best) {
+            if (overlaps(ws, pl->ws_best, gfeat, gelems * gfeat_es) ||
+                overlaps(ws, pl->ws_best, gout, size_prod({(uint64_t)f->B, (uint64_t)f->C, XY}) * 4) ||
+                overlaps(ws, pl->ws_best, l2i, (size_t)f->B * f->N * 64))
+                return FLASHBEV_ERR_ALIAS;
+            p.splits = (int32_t)sp;
+            p.part = reinterpret_cast<float *>(
+                reinterpret_cast<unsigned char *>(const_cast<void *>(ws)) + need);
+        }
+    }
+
     pl->prep_wgs = (gelems > 0) ? (int64_t)f->B * p.prep_tiles_per_b * p.prep_cblocks : 0;
     pl->gather_wgs = (gelems > 0) ? (p.groups + kGatherWaves - 1) / kGatherWaves : 0;
     if (pl->prep_wgs > 0x7FFFFFFFll || pl->gather_wgs > 0x7FFFFFFFll) return FLASHBEV_ERR_UNSUPPORTED;
@@ -2780,9 +2835,16 @@ int launch_bwd_gather(const BwdGatherPlan &pl, hipStream_t st)
         return FLASHBEV_ERR_HIP;
     if (pl.gather_wgs > 0 &&
         hipLaunchKernel(reinterpret_cast<const void *>(pick_gather(pl.lw, pl.vpl, pl.rows)),
-                        dim3((unsigned)pl.gather_wgs), dim3(kGatherWaves * kWave), args, pl.lds,
-                        st) != hipSuccess)
+                        dim3((unsigned)pl.gather_wgs, (unsigned)pl.prm.splits),
+                        dim3(kGatherWaves * kWave), args, pl.lds, st) != hipSuccess)
         return FLASHBEV_ERR_HIP;
+    if (pl.gather_wgs > 0 && pl.prm.splits > 1) {
+        const uint64_t wgs = (pl.prm.elems + 255) / 256;
+        if (hipLaunchKernel(reinterpret_cast<const void *>(sample_vt_bwd_join),
+                            dim3((unsigned)(wgs < 4096 ? wgs : 4096)), dim3(256), args, 0, st) !=
+            hipSuccess)
+            return FLASHBEV_ERR_HIP;
+    }
     return FLASHBEV_OK;
 }
 
@@ -2954,6 +3016,19 @@ extern "C" int flashbev_backward_workspace_size(const flashbev_features *feature
     return FLASHBEV_OK;
 }
 
+extern "C" int flashbev_backward_workspace_best(const flashbev_features *features,
+                                                const flashbev_bev_grid_spec *spec,
+                                                const flashbev_z_bins *z_bins, uint64_t *bytes)
+{
+    if (!bytes) return FLASHBEV_ERR_NULLPTR;
+    BwdGatherPlan pl;
+    const int rc = make_bwd_gather_plan(features, nullptr, spec, z_bins, nullptr, nullptr, nullptr,
+                                        0, false, &pl);
+    if (rc) return rc;
+    *bytes = pl.ws_best;
+    return FLASHBEV_OK;
+}
+
 // The no-allocation variant's workspace: a file-scope device array.  Host
 // code never takes the array's name as a device address (in host code it
 // names a host-side stand-in); the address on each device comes from
@@ -3003,7 +3078,7 @@ extern "C" int flashbev_sample_vt_backward_noalloc(const flashbev_features *feat
     rc = scratch_on_current_device(&ws);
     if (rc) return rc;
     rc = make_bwd_gather_plan(features, lidar2img, spec, z_bins, grad_out, grad_features, ws,
-                              (uint64_t)FLASHBEV_SCRATCH_BYTES, true, &pl);
+                              (uint64_t)FLASHBEV_SCRATCH_BYTES, true, &pl, true, FLASHBEV_F32, false);
     if (rc) return rc;
     return launch_bwd_gather(pl, reinterpret_cast<hipStream_t>(stream));
 }
