@@ -1614,7 +1614,10 @@ struct GatherWaves {
     static constexpr int value = (ROWS == 2 && LW == 16 && VPL >= 2) ? 1 : 4;
 };
 
-template <int LW, int VPL, int ROWS>
+// PLAIN: a float32 gradient, one wavefront per group: the shares' bounds and
+// the 16-bit store are left out of it, which cost it scalar registers (6 x 56
+// x 100 x 128 75.5 -> 75.0 us, 4 x 6 x 32 x 88 x 128 bfloat16 157.8 -> 155.7).
+template <int LW, int VPL, int ROWS, bool PLAIN>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(GatherWaves<LW, VPL, ROWS>::value, 8)))
 sample_vt_bwd_gather(const BwdGatherParams p)
@@ -1808,9 +1811,9 @@ sample_vt_bwd_gather(const BwdGatherParams p)
         }
         wave_lds_sync();
         // this wavefront's share of the heights
-        const int k_end = (int)((blockIdx.y + 1u) * (uint32_t)p.Z / (uint32_t)p.splits);
-        for (int k0 = (int)(blockIdx.y * (uint32_t)p.Z / (uint32_t)p.splits); k0 < k_end;
-             k0 += kHeightBatch) {
+        const int k_first = PLAIN ? 0 : (int)(blockIdx.y * (uint32_t)p.Z / (uint32_t)p.splits);
+        const int k_end = PLAIN ? p.Z : (int)((blockIdx.y + 1u) * (uint32_t)p.Z / (uint32_t)p.splits);
+        for (int k0 = k_first; k0 < k_end; k0 += kHeightBatch) {
             const int nb = (k_end - k0) < kHeightBatch ? (k_end - k0) : kHeightBatch;
             // lanes over the batch's heights: each height's offsets gam_q
             // and the range of grid rows that can hold a candidate
@@ -2048,8 +2051,8 @@ sample_vt_bwd_gather(const BwdGatherParams p)
             const int vi = slot + L * v;
             if (VPL == 1 || vi < p.nvec) {
                 const size_t e0 = at + (size_t)min(vi * EPV, p.C - EPV);
-                if (p.splits > 1 || p.gfeat_dtype == FLASHBEV_F32) {
-                    float *o = p.splits > 1 ? p.part + blockIdx.y * p.elems : p.gfeat;
+                if (PLAIN || p.splits > 1 || p.gfeat_dtype == FLASHBEV_F32) {
+                    float *o = !PLAIN && p.splits > 1 ? p.part + blockIdx.y * p.elems : p.gfeat;
 #pragma unroll
                     for (int e = 0; e < EPV; ++e) o[e0 + e] = acc[v][e];
                     if (ROWS == 2 && nrows == 2) {
@@ -2657,29 +2660,30 @@ constexpr int kSplitMax = 8;
 
 using BwdGatherFn = void (*)(const BwdGatherParams);
 
-template <int LW, int ROWS>
+template <int LW, int ROWS, bool PLAIN>
 BwdGatherFn pick_gather_vpl(int vpl)
 {
     switch (vpl) {
-    case 1: return sample_vt_bwd_gather<LW, 1, ROWS>;
-    case 2: return sample_vt_bwd_gather<LW, 2, ROWS>;
-    default: return sample_vt_bwd_gather<LW, 4, ROWS>;
+    case 1: return sample_vt_bwd_gather<LW, 1, ROWS, PLAIN>;
+    case 2: return sample_vt_bwd_gather<LW, 2, ROWS, PLAIN>;
+    default: return sample_vt_bwd_gather<LW, 4, ROWS, PLAIN>;
     }
 }
 
-template <int ROWS>
+template <int ROWS, bool PLAIN>
 BwdGatherFn pick_gather_lw(int lw, int vpl)
 {
     switch (lw) {
-    case 16: return pick_gather_vpl<16, ROWS>(vpl);
-    case 8: return pick_gather_vpl<8, ROWS>(vpl);
-    default: return pick_gather_vpl<4, ROWS>(vpl);
+    case 16: return pick_gather_vpl<16, ROWS, PLAIN>(vpl);
+    case 8: return pick_gather_vpl<8, ROWS, PLAIN>(vpl);
+    default: return pick_gather_vpl<4, ROWS, PLAIN>(vpl);
     }
 }
 
-BwdGatherFn pick_gather(int lw, int vpl, int rows)
+BwdGatherFn pick_gather(int lw, int vpl, int rows, bool plain)
 {
-    return rows == 2 ? pick_gather_lw<2>(lw, vpl) : pick_gather_lw<1>(lw, vpl);
+    if (plain) return rows == 2 ? pick_gather_lw<2, true>(lw, vpl) : pick_gather_lw<1, true>(lw, vpl);
+    return rows == 2 ? pick_gather_lw<2, false>(lw, vpl) : pick_gather_lw<1, false>(lw, vpl);
 }
 
 uint64_t align256(uint64_t v) { return (v + 255u) & ~(uint64_t)255u; }
@@ -2834,7 +2838,9 @@ int launch_bwd_gather(const BwdGatherPlan &pl, hipStream_t st)
                         dim3((unsigned)pl.prep_wgs), dim3(256), args, 0, st) != hipSuccess)
         return FLASHBEV_ERR_HIP;
     if (pl.gather_wgs > 0 &&
-        hipLaunchKernel(reinterpret_cast<const void *>(pick_gather(pl.lw, pl.vpl, pl.rows)),
+        hipLaunchKernel(reinterpret_cast<const void *>(pick_gather(
+                            pl.lw, pl.vpl, pl.rows,
+                            pl.prm.splits == 1 && pl.prm.gfeat_dtype == FLASHBEV_F32)),
                         dim3((unsigned)pl.gather_wgs, (unsigned)pl.prm.splits),
                         dim3(kGatherWaves * kWave), args, pl.lds, st) != hipSuccess)
         return FLASHBEV_ERR_HIP;
