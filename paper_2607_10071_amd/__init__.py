@@ -161,6 +161,7 @@ def _lib():
         L.flashsca_backward_ws.restype = ctypes.c_int
         L.flashsca_backward_launch_info.argtypes = L.flashsca_launch_info.argtypes
         L.flashsca_backward_launch_info.restype = ctypes.c_int
+        L._packed_calls = {}
         _LIB = L
     return _LIB
 
@@ -174,19 +175,20 @@ _PACK_ZBINS = struct.Struct("@Pi0P")
 _PACK_SCA = struct.Struct("@P24i")
 assert _PACK_FEATURES.size == ctypes.sizeof(Features) and _PACK_GRID.size == ctypes.sizeof(GridSpec)
 assert _PACK_ZBINS.size == ctypes.sizeof(ZBins) and _PACK_SCA.size == ctypes.sizeof(ScaValue)
-_PACKED_CALLS = {}
 
 
 def _packed_call(name: str, args):
     """The C entry point ``name`` with every pointer taken as an address or as
-    bytes (``args``: P for pointers, i for int32, Q for uint64)."""
-    fn = _PACKED_CALLS.get(name)
+    bytes (``args``: P for pointers, i for int32, Q for uint64).  The library
+    that is loaded keeps it."""
+    lib = _lib()
+    fn = lib._packed_calls.get(name)
     if fn is None:
         kinds = {"P": ctypes.c_void_p, "i": ctypes.c_int32, "Q": ctypes.c_uint64}
-        fn = _lib()[name]
+        fn = lib[name]
         fn.argtypes = [kinds[k] for k in args]
         fn.restype = ctypes.c_int
-        _PACKED_CALLS[name] = fn
+        lib._packed_calls[name] = fn
     return fn
 
 

@@ -73,3 +73,19 @@ def test_gradient_types_of_the_gather_form():
     assert call(*args(base + 4096 - 32, fb.DTYPE_CODES["bf16"], base + (1 << 24) + 1)) == S["ERR_ALIGN"]
     assert call(*args(base + 4096 - 30, fb.DTYPE_CODES["bf16"], base + (1 << 24))) == S["ERR_ALIAS"]
     assert call(None, *args(0, 0, 0)[1:]) == S["ERR_NULLPTR"]
+
+
+def test_packed_calls_belong_to_the_loaded_library():
+    # the phase-clock tool loads another build of the library and goes back
+    from paper_2607_10071_amd import phases
+    address = lambda: ctypes.cast(fb._packed_call("flashbev_sample_vt", "PPPPPP"),
+                                  ctypes.c_void_p).value
+    of = lambda lib: ctypes.cast(lib["flashbev_sample_vt"], ctypes.c_void_p).value
+    plain_path, plain = fb._LIB_PATH, fb._lib()
+    assert address() == of(plain)
+    try:
+        fb._LIB_PATH, fb._LIB = phases.LIB_PATH, None
+        assert address() == of(fb._lib()) != of(plain)
+    finally:
+        fb._LIB_PATH, fb._LIB = plain_path, plain
+    assert address() == of(plain)
