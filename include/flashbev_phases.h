@@ -22,7 +22,8 @@
  * 7 barrier, 8 end, 9 rounds (groups of cells), 10 projection passes,
  * 11 the wavefront's HW_ID register (SIMD, CU, shader array, shader engine)
  * in bits 0..31 and its XCC_ID register (the XCD) in bits 32..63, 12 the
- * valid samples of its groups, 13..15 zero.
+ * valid samples of its groups (their records where heights are merged),
+ * 13..15 zero.
  */
 #ifndef FLASHBEV_PHASES_H
 #define FLASHBEV_PHASES_H
@@ -46,7 +47,8 @@ int flashbev_phase_log(void *log);
 /*
  * The same for the FlashSCA backward (include/flashsca.h, flashsca_backward;
  * the BEVFormer spatial cross-attention of Sec. 4.5): lane 0 of every
- * wavefront of its kernel sums the real-time counter over the kernel's steps.
+ * wavefront of its kernel sums the real-time counter over the kernel's steps
+ * (the scatter form's; the binned form has no clock).
  * Memory of at least workgroups * (threads_per_workgroup / 64) * 16 unsigned
  * 64-bit words (flashsca_backward_launch_info), written at
  * [(workgroup * waves + wave) * 16 + slot]; NULL stops the recording.

@@ -29,8 +29,10 @@ Clock ticks are 10 ns (the 100 MHz real-time counter).
 
     python -m paper_2607_10071_amd.phases --sca-backward P [P ...]
 
-runs the FlashSCA backward at BEVFormer-base defaults for each point count P
-through the same library (its phase clock, ``flashsca_phase_log``) and prints,
+runs the FlashSCA backward's scatter form (the kernel that has the clock; the
+binned form, which large calls take by default, has none) at BEVFormer-base
+defaults for each point count P through the same library (its phase clock,
+``flashsca_phase_log``) and prints,
 per P, the mean time per wavefront in each step of that kernel (projection,
 set-up, chunk records, point gradients, merge-table inserts and the barrier
 after them, the walk of the distinct rows with its float atomics and the
@@ -55,9 +57,18 @@ TICK_US = 0.01
 PHASES = ("staging", "projection", "setup", "pad", "gather", "stash", "barrier", "store")
 
 
+def recorded(log: np.ndarray) -> np.ndarray:
+    """The wavefronts that wrote a clock record."""
+    live = log[:, 0] > 0
+    if not live.any():
+        raise RuntimeError("no wavefront wrote a clock record: the calls ran a kernel or a "
+                           "library without the clock")
+    return live
+
+
 def phase_table(log: np.ndarray) -> dict:
     """Per-phase statistics from clock records [waves, 16] (int64 ticks)."""
-    live = log[:, 0] > 0
+    live = recorded(log)
     d = log[live].astype(np.float64)
     start, staged, barrier, end = d[:, 0], d[:, 1], d[:, 7], d[:, 8]
     per = {
@@ -148,7 +159,7 @@ def run(names, calls: int = 5, device: str = "cuda:0") -> list:
                     logs.append(buf.cpu().numpy().reshape(waves, SLOTS).copy())
             spans, spreads = [], []
             for lg in logs:
-                live = lg[:, 0] > 0
+                live = recorded(lg)
                 spans.append((lg[live, 8].max() - lg[live, 0].min()) * TICK_US)
                 spreads.append((lg[live, 0].max() - lg[live, 0].min()) * TICK_US)
             rec = {"workload": name,
@@ -176,7 +187,7 @@ SCA_STEPS = (("projection", 1), ("setup", 2), ("records", 3), ("point_gradients"
 def sca_backward_table(log: np.ndarray) -> dict:
     """Per-step statistics of the FlashSCA backward from clock records
     [waves, 16] (int64)."""
-    live = log[:, 0] > 0
+    live = recorded(log)
     d = log[live].astype(np.float64)
     life = d[:, 13] - d[:, 0]
     total = sum(d[:, k].sum() for _, k in SCA_STEPS)
@@ -224,7 +235,8 @@ def run_sca_backward(points, calls: int = 3, device: str = "cuda:0") -> list:
                 fb._LIB_PATH, fb._LIB = path, None
                 stream = torch.cuda.current_stream(dev)
                 call = fb.prepare_sca_backward(v, l2i, inst.z, grid, img, wl.levels, wl.heads,
-                                               off, lg, g, gv, go, gl, stream=stream)
+                                               off, lg, g, gv, go, gl, stream=stream,
+                                               method="scatter")
                 best = float("inf")
                 for _ in range(3):
                     for _ in range(5):
@@ -254,14 +266,15 @@ def run_sca_backward(points, calls: int = 3, device: str = "cuda:0") -> list:
                     if lib.flashsca_phase_log(ctypes.c_void_p(buf.data_ptr())) != 0:
                         raise RuntimeError("flashsca_phase_log failed")
                     fb.sca_backward(v, l2i, inst.z, grid, img, wl.levels, wl.heads, off, lg, g,
-                                    grad_value=gv, grad_offsets=go, grad_logits=gl)
+                                    grad_value=gv, grad_offsets=go, grad_logits=gl,
+                                    method="scatter")
                     torch.cuda.synchronize()
                     if lib.flashsca_phase_log(None) != 0:
                         raise RuntimeError("flashsca_phase_log failed")
                     logs.append(buf.cpu().numpy().reshape(waves, SLOTS).copy())
             spans = []
             for lg_ in logs:
-                live = lg_[:, 0] > 0
+                live = recorded(lg_)
                 spans.append((lg_[live, 13].max() - lg_[live, 0].min()) * TICK_US)
             rec = {"sca_backward": f"BEVFormer-base P={P}",
                    "config": f"B={wl.B} N={wl.N} C={wl.C} {wl.dtype} heads={wl.heads} "
