@@ -207,7 +207,7 @@ int flashbev_sample_vt_backward(const flashbev_features *features, const float *
  *                  (float32, B X Y C), then at the next 256-byte boundary
  *                  den_z (uint8, B X Y Z).
  *   workspace_bytes  its size; flashbev_backward_workspace_size gives the
- *                  minimum.
+ *                  minimum, and no more than that is touched.
  *
  * Errors (before any HIP call): those of flashbev_sample_vt_backward;
  * FLASHBEV_ERR_NULLPTR if workspace is NULL, FLASHBEV_ERR_ALIGN if it is not
@@ -227,7 +227,8 @@ int flashbev_sample_vt_backward_ws(const flashbev_features *features, const floa
  * flashbev_sample_vt_backward_ws with the gradient stored as `grad_dtype`:
  * FLASHBEV_F32, or the features' dtype (the float32 sum of each element
  * rounded once to nearest even), aligned to it.  FLASHBEV_ERR_DTYPE for any
- * other type.
+ * other type.  A workspace of flashbev_backward_workspace_best bytes or more
+ * is used up to those (which no other buffer may then overlap).
  */
 int flashbev_sample_vt_backward_ws_as(const flashbev_features *features, const float *lidar2img,
                                       const flashbev_bev_grid_spec *spec,
@@ -260,11 +261,10 @@ int flashbev_sample_vt_backward_noalloc(const flashbev_features *features,
                                         const flashbev_z_bins *z_bins, const float *grad_out,
                                         float *grad_features, void *stream);
 
-/* Workspace bytes with which flashbev_sample_vt_backward_ws and _ws_as run
- * fastest: on small maps the minimum below and room for partial sums, with
- * which several wavefronts share a pixel group's heights (their sums are added
- * in a fixed order, which is not the order of a smaller workspace's call).
- * The room must overlap no other buffer. */
+/* Workspace bytes with which flashbev_sample_vt_backward_ws_as runs fastest: on
+ * small maps the minimum below and room for partial sums, with which several
+ * wavefronts share a pixel group's heights (their sums are added in a fixed
+ * order, which is not the order of a smaller workspace's call). */
 int flashbev_backward_workspace_best(const flashbev_features *features,
                                      const flashbev_bev_grid_spec *spec,
                                      const flashbev_z_bins *z_bins, uint64_t *bytes);

@@ -433,13 +433,16 @@ def sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_hw: Tuple
     features_shape  (B, N, H, W, C) of the features of the forward call.
     features_dtype  their dtype ("f32", "f16", "bf16" or a torch dtype).
     grad_features   optional CUDA float32 tensor [B, N, H, W, C] to write.
-    method          "gather" (flashbev_sample_vt_backward_ws: every gradient
-                    row written once, no atomics, bitwise reproducible; it
-                    needs a device workspace, allocated here unless
-                    ``workspace`` is given) or "scatter"
+    method          "gather" (flashbev_sample_vt_backward_ws_as: every
+                    gradient row written once, no atomics, bitwise
+                    reproducible; it needs a device workspace, allocated here
+                    unless ``workspace`` is given) or "scatter"
                     (flashbev_sample_vt_backward: float atomics, no
                     workspace).  "gather" falls back to "scatter" for
                     shapes it does not serve.
+    workspace       optional device tensor of at least
+                    backward_workspace_size bytes, of which only those are
+                    used (no height is shared by several wavefronts then).
 
     Returns ``grad_features`` (float32, channel-last).  Asynchronous.
     """
@@ -476,19 +479,21 @@ def _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shap
             if workspace is None:
                 best = ctypes.c_uint64()
                 _packed_call("flashbev_backward_workspace_best", "PPPP")(f, g, zb, ctypes.byref(best))
-                workspace = torch.empty(max(need, best.value, 1), dtype=torch.uint8,
-                                        device=grad_out.device)
+                room = max(need, best.value, 1)
+                workspace = torch.empty(room, dtype=torch.uint8, device=grad_out.device)
             elif not workspace.is_cuda or workspace.numel() * workspace.element_size() < need:
                 raise ValueError(f"workspace must be a device tensor of at least {need} bytes")
+            else:
+                room = need   # the rest of the caller's tensor may hold other things
             if convert:
                 grad_features = torch.empty((B, N, H, W, C), dtype=grad_dtype, device=grad_out.device)
             call = _packed_call("flashbev_sample_vt_backward_ws_as", "PPPPPPiPQP")
             with _on_device(dev):
                 rc = call(f, lidar2img.data_ptr(), g, zb, grad_out.data_ptr(),
                           grad_features.data_ptr(), _dtype_code(grad_features),
-                          workspace.data_ptr(), workspace.numel() * workspace.element_size(), s)
+                          workspace.data_ptr(), room, s)
             if rc != 0:
-                raise FlashBevError(rc, "flashbev_sample_vt_backward_ws")
+                raise FlashBevError(rc, "flashbev_sample_vt_backward_ws_as")
             return grad_features
     if convert:
         grad_features = torch.empty((B, N, H, W, C), dtype=torch.float32, device=grad_out.device)
@@ -691,11 +696,12 @@ def prepare_sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_h
             ws = torch.empty(max(need, best.value, 1), dtype=torch.uint8, device=grad_out.device)
             args = (ctypes.byref(f), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
                     ctypes.byref(zb), ctypes.c_void_p(grad_out.data_ptr()),
-                    ctypes.c_void_p(grad_features.data_ptr()), ctypes.c_void_p(ws.data_ptr()),
+                    ctypes.c_void_p(grad_features.data_ptr()),
+                    ctypes.c_int32(DTYPE_CODES["f32"]), ctypes.c_void_p(ws.data_ptr()),
                     ctypes.c_uint64(ws.numel()), ctypes.c_void_p(s))
-            return _Prepared(_lib().flashbev_sample_vt_backward_ws, args,
+            return _Prepared(_packed_call("flashbev_sample_vt_backward_ws_as", "PPPPPPiPQP"), args,
                              (grad_out, lidar2img, grad_features, ws, z, f, g, zb),
-                             "flashbev_sample_vt_backward_ws", dev)
+                             "flashbev_sample_vt_backward_ws_as", dev)
     args = (ctypes.byref(f), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
             ctypes.byref(zb), ctypes.c_void_p(grad_out.data_ptr()),
             ctypes.c_void_p(grad_features.data_ptr()), ctypes.c_void_p(s))

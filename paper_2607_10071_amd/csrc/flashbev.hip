@@ -2689,7 +2689,9 @@ BwdGatherFn pick_gather(int lw, int vpl, int rows, bool plain)
 uint64_t align256(uint64_t v) { return (v + 255u) & ~(uint64_t)255u; }
 
 // All argument checks of the gather-form backward, the workspace's layout
-// and size.  `need_data` requires the device pointers (and the workspace).
+// and size.  `need_data` requires the device pointers (and the workspace);
+// `split` lets the call use workspace beyond the minimum (shared heights),
+// which callers of the entry points without it may hold other things in.
 int make_bwd_gather_plan(const flashbev_features *f, const float *l2i,
                          const flashbev_bev_grid_spec *s, const flashbev_z_bins *zb,
                          const float *gout, const float *gfeat, const void *ws, uint64_t ws_bytes,
@@ -3099,7 +3101,7 @@ extern "C" int flashbev_sample_vt_backward_ws(const flashbev_features *features,
 {
     BwdGatherPlan pl;
     const int rc = make_bwd_gather_plan(features, lidar2img, spec, z_bins, grad_out, grad_features,
-                                        workspace, workspace_bytes, true, &pl);
+                                        workspace, workspace_bytes, true, &pl, true, FLASHBEV_F32, false);
     if (rc) return rc;
     return launch_bwd_gather(pl, reinterpret_cast<hipStream_t>(stream));
 }
