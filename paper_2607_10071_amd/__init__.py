@@ -875,7 +875,10 @@ def prepare_sca_forward(value, lidar2img, anchors, grid: BevGrid, img_hw, levels
                      dev)
 
 
-def _sca_bwd_outputs(value, Q, heads, L, P, grad_value, grad_offsets, grad_logits, want):
+def _sca_bwd_outputs(value, Q, heads, L, P, grad_value, grad_offsets, grad_logits, want,
+                     value_dtype=None):
+    """The gradients by name: those given, checked, and those in ``want`` made
+    (the value's in ``value_dtype``, float32 by default)."""
     import torch
 
     B, N, S, C = value.shape
@@ -887,8 +890,9 @@ def _sca_bwd_outputs(value, Q, heads, L, P, grad_value, grad_offsets, grad_logit
     for k in ("value", "offsets", "logits"):
         t = given[k]
         if t is None and k in want:
-            t = torch.empty(shapes[k], dtype=torch.float32, device=dev)
-        if t is not None and (t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda
+            t = torch.empty(shapes[k], dtype=(k == "value" and value_dtype) or torch.float32,
+                            device=dev)
+        elif t is not None and (t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda
                               or tuple(t.shape) != shapes[k]):
             raise ValueError(f"grad_{k} must be a contiguous float32 device tensor {shapes[k]}")
         out[k] = t
@@ -978,16 +982,15 @@ def _sca_backward(value, lidar2img, anchors, grid, img_hw, levels, heads, offset
     s = _stream_handle(stream, dev)
     wants_value = grad_value is not None or "value" in want
     need = _sca_workspace_bytes(v, g, zb, P, method, logits.numel(), wants_value or None)
-    ws = _sca_workspace(need, dev, s) if need >= 0 else None
     convert = value_dtype is not None and value_dtype != torch.float32 and wants_value
-    if convert and ws is not None:
-        grad_value = torch.empty((B, N, S, C), dtype=value_dtype, device=dev)
-        outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, None, grad_offsets, grad_logits,
-                                tuple(k for k in want if k != "value"))
-        outs["value"] = grad_value
-    else:
-        outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,
-                                grad_logits, want)
+    # the gradients first: where the device has no room left for a workspace,
+    # the scatter form runs without one
+    outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,
+                            grad_logits, want, value_dtype if convert and need >= 0 else None)
+    ws = _sca_workspace(need, dev, s) if need >= 0 else None
+    if convert and need >= 0 and ws is None:
+        del outs["value"]   # float32 sums, converted below
+        outs["value"] = torch.empty((B, N, S, C), dtype=torch.float32, device=dev)
     ptr = lambda t: t.data_ptr() if t is not None else 0
     ins = (v, lidar2img.data_ptr(), g, zb, P, offsets.data_ptr(), logits.data_ptr(),
            grad_out.data_ptr(), ptr(outs["value"]))

@@ -1,12 +1,15 @@
-"""Device workspaces of the backwards: how much of a caller's own is used."""
+"""Device workspaces of the backwards: how much of a caller's own is used, and
+what happens where the device has no room for one."""
 import ctypes
 
 import numpy as np
 import pytest
 
+import oracle
 import synth
 import test_gpu_backward as tb
 import test_gpu_parity as tp
+import test_gpu_sca_backward as ts
 
 pytestmark = pytest.mark.gpu
 
@@ -15,6 +18,29 @@ pytestmark = pytest.mark.gpu
 def fb():
     import paper_2607_10071_amd as m
     return m
+
+
+@pytest.fixture
+def room(monkeypatch):
+    """room(n): from here on torch.empty raises OutOfMemoryError where more
+    than n bytes of its tensors would be alive."""
+    import torch
+    import weakref
+
+    kept = torch.empty
+    live = [0]
+
+    def limit(n):
+        def empty(*a, **kw):
+            t = kept(*a, **kw)
+            size = t.numel() * t.element_size()
+            if live[0] + size > n:
+                raise torch.cuda.OutOfMemoryError(f"{live[0]} + {size} > {n} bytes")
+            live[0] += size
+            weakref.finalize(t, lambda: live.__setitem__(0, live[0] - size))
+            return t
+        monkeypatch.setattr(torch, "empty", empty)
+    return limit
 
 
 class VT:
@@ -46,6 +72,31 @@ class VT:
         tb.assert_bwd_parity(grad.float().cpu().numpy(), ref, scale, terms, what)
 
 
+class SCA:
+    """A FlashSCA backward of enough points for the binned form."""
+
+    def __init__(self, fb, device, dtype="f32"):
+        import torch
+        self.inst = ts.small(27, levels=((29, 50), (15, 25)), C=256, heads=8, P=8, Z=4, X=64, Y=64,
+                             x_min=-32.0, dx=1.0, y_min=-32.0, dy=1.0, dtype=dtype)
+        wl = self.wl = self.inst.wl
+        assert wl.B * wl.Q * wl.heads * wl.L * wl.P >= fb.SCA_BINNED_MIN_POINTS
+        self.v, self.l2i, self.off, self.lg = ts._dev(self.inst, device)
+        self.g = ts._g(wl)
+        self.gt = torch.from_numpy(self.g).to(device)
+        self.args = (self.v, self.l2i, self.inst.z, fb.grid_of(wl), (wl.img_h, wl.img_w),
+                     wl.levels, wl.heads, self.off, self.lg, self.gt)
+        st = fb._sca_structs(self.v.shape, fb._dtype_code(self.v), 0, wl.heads, wl.levels,
+                             (wl.img_h, wl.img_w), fb.grid_of(wl), fb._z_array(self.inst.z), "mean")
+        self.need = fb._sca_workspace_bytes(*map(ctypes.byref, st), wl.P, "auto", self.lg.numel(),
+                                            True)
+        assert self.need > 0
+
+    def check(self, r, what):
+        ref = oracle.sca_backward_instance(self.inst, self.g, "mean")
+        ts.assert_bwd_parity({k: t.cpu().numpy() for k, t in r.items()}, ref, self.wl, what)
+
+
 def test_a_larger_workspace_is_used_up_to_the_minimum(fb, device):
     """flashbev_sample_vt_backward_ws touches the minimum only: an arena may
     hold the gradient behind it, and the sums' order does not depend on its
@@ -68,3 +119,17 @@ def test_a_larger_workspace_is_used_up_to_the_minimum(fb, device):
     grad.fill_(7.0)
     b = fb.sample_vt_backward(*c.args, grad_features=grad, workspace=arena)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_sca_backward_without_room_for_a_workspace(fb, device, room, dtype):
+    """Memory for the float32 gradients alone is enough (the scatter form)."""
+    import torch
+    c = SCA(fb, device, dtype)
+    room(max(c.need, 4 * (c.v.numel() + c.off.numel() + c.lg.numel())))
+    r = fb._sca_backward(*c.args, None, None, None, ("value", "offsets", "logits"), "mean", None,
+                         "auto", c.v.dtype)
+    torch.cuda.synchronize()
+    assert r["value"].dtype == c.v.dtype
+    if dtype == "f32":
+        c.check(r, "no room")
