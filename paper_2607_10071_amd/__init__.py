@@ -414,6 +414,21 @@ def _backward_workspace_bytes(f, g, zb, args) -> int:
     return int(out.value)
 
 
+def _backward_workspace(f, g, zb, need: int, device):
+    """A workspace for the gather form: with room for shared heights, or, where
+    the device has none, of the ``need`` bytes that the call cannot do without."""
+    import torch
+
+    best = ctypes.c_uint64()
+    _packed_call("flashbev_backward_workspace_best", "PPPP")(f, g, zb, ctypes.byref(best))
+    if best.value > need:
+        try:
+            return torch.empty(best.value, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+
+
 def _dtype_name(features_dtype) -> str:
     import torch
 
@@ -476,17 +491,15 @@ def _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shap
         if need < 0:
             method = "scatter"
         else:
+            if convert:
+                grad_features = torch.empty((B, N, H, W, C), dtype=grad_dtype, device=grad_out.device)
             if workspace is None:
-                best = ctypes.c_uint64()
-                _packed_call("flashbev_backward_workspace_best", "PPPP")(f, g, zb, ctypes.byref(best))
-                room = max(need, best.value, 1)
-                workspace = torch.empty(room, dtype=torch.uint8, device=grad_out.device)
+                workspace = _backward_workspace(f, g, zb, need, dev)
+                room = workspace.numel()
             elif not workspace.is_cuda or workspace.numel() * workspace.element_size() < need:
                 raise ValueError(f"workspace must be a device tensor of at least {need} bytes")
             else:
                 room = need   # the rest of the caller's tensor may hold other things
-            if convert:
-                grad_features = torch.empty((B, N, H, W, C), dtype=grad_dtype, device=grad_out.device)
             call = _packed_call("flashbev_sample_vt_backward_ws_as", "PPPPPPiPQP")
             with _on_device(dev):
                 rc = call(f, lidar2img.data_ptr(), g, zb, grad_out.data_ptr(),
@@ -690,10 +703,7 @@ def prepare_sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_h
     if method == "gather":
         need = backward_workspace_size((B, N, H, W, C), features_dtype, z, grid, img_hw, reduce)
         if need >= 0:
-            best = ctypes.c_uint64()
-            _packed_call("flashbev_backward_workspace_best", "PPPP")(
-                ctypes.byref(f), ctypes.byref(g), ctypes.byref(zb), ctypes.byref(best))
-            ws = torch.empty(max(need, best.value, 1), dtype=torch.uint8, device=grad_out.device)
+            ws = _backward_workspace(ctypes.byref(f), ctypes.byref(g), ctypes.byref(zb), need, dev)
             args = (ctypes.byref(f), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
                     ctypes.byref(zb), ctypes.c_void_p(grad_out.data_ptr()),
                     ctypes.c_void_p(grad_features.data_ptr()),

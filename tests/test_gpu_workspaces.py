@@ -121,6 +121,34 @@ def test_a_larger_workspace_is_used_up_to_the_minimum(fb, device):
     assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("call", ["plain", "prepared", "bf16"])
+def test_gather_backward_without_room_for_shared_heights(fb, device, room, call):
+    """Memory for the gradient and the smallest workspace is enough."""
+    import torch
+    c = VT(fb, device)
+    grad = torch.empty(c.shape, device=device)
+    size = grad.numel() * 4
+    assert c.best > c.need + size
+    if call == "prepared":
+        room(c.need)
+        fb.prepare_sample_vt_backward(*c.args, grad)()
+    elif call == "plain":
+        room(c.need + size)
+        grad = fb.sample_vt_backward(*c.args)
+    else:
+        least = torch.empty(c.need, dtype=torch.uint8, device=device)
+        want = fb.sample_vt_backward(*c.args[:6], "bf16", workspace=least).bfloat16()
+        room(c.need + size // 2)
+        grad = fb._sample_vt_backward(*c.args[:6], "bf16", None, "mean", None, "gather", None,
+                                      torch.bfloat16)
+    torch.cuda.synchronize()
+    if call == "bf16":
+        assert grad.dtype == torch.bfloat16
+        assert torch.equal(grad, want)
+    else:
+        c.check(grad, f"no room, {call}")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_sca_backward_without_room_for_a_workspace(fb, device, room, dtype):
     """Memory for the float32 gradients alone is enough (the scatter form)."""
