@@ -918,14 +918,14 @@ SCA_BINNED_MIN_POINTS = 1 << 18
 
 
 def _sca_workspace_bytes(v, g, zb, P: int, method: str, points: int, grad_value) -> int:
-    """Workspace bytes of the binned backward, or -1 where the scatter form
-    is taken: "auto" takes it for few points, for calls that want no value
-    gradient (the two are one kernel there), and for shapes the binned form
-    does not serve."""
+    """Workspace bytes of the binned backward, or -1 where flashsca_backward
+    is taken: for calls that want no value gradient (which has nothing to bin;
+    both forms are one kernel there), with "auto" for few points, and for
+    shapes that the binned form does not serve."""
     if method not in SCA_BACKWARD_METHODS:
         raise ValueError(f"method must be one of {SCA_BACKWARD_METHODS}")
-    if method == "scatter" or (method == "auto" and (grad_value is None
-                                                     or points < SCA_BINNED_MIN_POINTS)):
+    if method == "scatter" or grad_value is None or (method == "auto"
+                                                     and points < SCA_BINNED_MIN_POINTS):
         return -1
     out = ctypes.c_uint64()
     rc = _packed_call("flashsca_backward_workspace_size", "PPPiP")(v, g, zb, P, ctypes.byref(out))

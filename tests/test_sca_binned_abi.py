@@ -81,3 +81,6 @@ def test_python_method_argument():
     assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "auto", big, None) == -1
     assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "auto", big, True) == size()[1]
     assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "scatter", big, True) == -1
+    # nothing to bin without a value gradient: no workspace
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "binned", big, None) == -1
+    assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "binned", 1, True) == size()[1]
