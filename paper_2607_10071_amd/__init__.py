@@ -414,7 +414,20 @@ def _backward_workspace_bytes(f, g, zb, args) -> int:
     return int(out.value)
 
 
-def _backward_workspace(f, g, zb, need: int, device):
+def _workspace(size: int, device, s: int):
+    """``size`` bytes of device memory from the pool of the stream ``s``, so
+    that what the allocator gives out before and after a call on ``s`` is in
+    order with it.  (A block of another stream's pool may still be in use
+    there, and would go back to that stream while the call runs on ``s``.)"""
+    import torch
+
+    if s == torch._C._cuda_getCurrentRawStream(device.index):
+        return torch.empty(size, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(torch.cuda.ExternalStream(s, device=device)):
+        return torch.empty(size, dtype=torch.uint8, device=device)
+
+
+def _backward_workspace(f, g, zb, need: int, device, s: int):
     """A workspace for the gather form: with room for shared heights, or, where
     the device has none, of the ``need`` bytes that the call cannot do without."""
     import torch
@@ -423,10 +436,10 @@ def _backward_workspace(f, g, zb, need: int, device):
     _packed_call("flashbev_backward_workspace_best", "PPPP")(f, g, zb, ctypes.byref(best))
     if best.value > need:
         try:
-            return torch.empty(best.value, dtype=torch.uint8, device=device)
+            return _workspace(best.value, device, s)
         except torch.cuda.OutOfMemoryError:
             pass
-    return torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+    return _workspace(max(need, 1), device, s)
 
 
 def _dtype_name(features_dtype) -> str:
@@ -494,7 +507,7 @@ def _sample_vt_backward(grad_out, lidar2img, z_bins, grid, img_hw, features_shap
             if convert:
                 grad_features = torch.empty((B, N, H, W, C), dtype=grad_dtype, device=grad_out.device)
             if workspace is None:
-                workspace = _backward_workspace(f, g, zb, need, dev)
+                workspace = _backward_workspace(f, g, zb, need, dev, s)
                 room = workspace.numel()
             elif not workspace.is_cuda or workspace.numel() * workspace.element_size() < need:
                 raise ValueError(f"workspace must be a device tensor of at least {need} bytes")
@@ -703,7 +716,8 @@ def prepare_sample_vt_backward(grad_out, lidar2img, z_bins, grid: BevGrid, img_h
     if method == "gather":
         need = backward_workspace_size((B, N, H, W, C), features_dtype, z, grid, img_hw, reduce)
         if need >= 0:
-            ws = _backward_workspace(ctypes.byref(f), ctypes.byref(g), ctypes.byref(zb), need, dev)
+            ws = _backward_workspace(ctypes.byref(f), ctypes.byref(g), ctypes.byref(zb), need, dev,
+                                     s)
             args = (ctypes.byref(f), ctypes.c_void_p(lidar2img.data_ptr()), ctypes.byref(g),
                     ctypes.byref(zb), ctypes.c_void_p(grad_out.data_ptr()),
                     ctypes.c_void_p(grad_features.data_ptr()),
@@ -937,17 +951,14 @@ def _sca_workspace_bytes(v, g, zb, P: int, method: str, points: int, grad_value)
 
 
 def _sca_workspace(need: int, device, s: int):
-    """The binned backward's workspace, held for the stream that uses it; None
-    where the device has no room for it (the scatter form needs none)."""
+    """The binned backward's workspace for a call on the stream ``s``; None where
+    the device has no room for it (the scatter form needs none)."""
     import torch
 
     try:
-        ws = torch.empty(need, dtype=torch.uint8, device=device)
+        return _workspace(need, device, s)
     except torch.cuda.OutOfMemoryError:
         return None
-    if s != torch.cuda.current_stream(device).cuda_stream:
-        ws.record_stream(torch.cuda.ExternalStream(s, device=device))
-    return ws
 
 
 def sca_backward(value, lidar2img, anchors, grid: BevGrid, img_hw, levels, heads: int, offsets,

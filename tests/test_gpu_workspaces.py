@@ -1,5 +1,5 @@
-"""Device workspaces of the backwards: how much of a caller's own is used, and
-what happens where the device has no room for one."""
+"""Device workspaces of the backwards: how much of a caller's own is used, what
+happens where the device has no room for one, and which stream holds it."""
 import ctypes
 
 import numpy as np
@@ -161,3 +161,46 @@ def test_sca_backward_without_room_for_a_workspace(fb, device, room, dtype):
     assert r["value"].dtype == c.v.dtype
     if dtype == "f32":
         c.check(r, "no room")
+
+
+@pytest.mark.parametrize("op", ["vt", "vt prepared", "sca", "sca prepared"])
+def test_a_workspace_belongs_to_the_stream_of_its_call(fb, device, op, monkeypatch):
+    """A call on another stream than the current one: its workspace is neither
+    a block that the current stream's work may still be using nor one that the
+    current stream is given next, when the other may still be using it."""
+    import torch
+    c = SCA(fb, device) if op.startswith("sca") else VT(fb, device)
+    size = c.need if op.startswith("sca") else c.best
+    out = [torch.empty(t, device=device) for t in
+           ((c.v.shape, c.off.shape, c.lg.shape) if op == "sca prepared" else (c.shape,) if op.startswith("vt") else ())]
+    s = torch.cuda.Stream(device)
+    kept, seen = torch.empty, []
+
+    def empty(*a, **kw):
+        t = kept(*a, **kw)
+        if kw.get("dtype") is torch.uint8:
+            seen.append(t.data_ptr())
+        return t
+
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    block = torch.empty(size, dtype=torch.uint8, device=device)
+    freed = block.data_ptr()
+    del block   # the current stream's pool holds a block of the workspace's size
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", empty)
+        if op == "vt":
+            r = fb.sample_vt_backward(*c.args, grad_features=out[0], stream=s)
+        elif op == "sca":
+            r = fb.sca_backward(*c.args, stream=s)
+        elif op == "vt prepared":
+            r = out[0]
+            fb.prepare_sample_vt_backward(*c.args, r, stream=s)()
+        else:
+            r = dict(zip(("value", "offsets", "logits"), out))
+            fb.prepare_sca_backward(*c.args, *out, stream=s)()
+    assert len(seen) == 1 and seen[0] != freed
+    after = [torch.empty(size, dtype=torch.uint8, device=device) for _ in range(2)]
+    assert seen[0] not in [t.data_ptr() for t in after]
+    s.synchronize()
+    c.check(r, op)
