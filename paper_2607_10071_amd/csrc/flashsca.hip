@@ -1225,10 +1225,7 @@ __global__ void __launch_bounds__(256) sca_bin_alloc(const ScaParams p)
     at = __shfl(at, lead) + upto - ns;
     mb = __shfl(mb, lead) + (uint32_t)__popcll(bins & ((1ull << lane) - 1ull));
     if (!many) return;
-    if (slot + ns > p.slice_cap || at + ns > p.slice_cap || mb >= p.slice_cap) {
-        p.misc[kMiscFull] = 1u;
-        return;
-    }
+    // within slice_cap, which holds the slices of any bins whose records fit
     p.multi[mb] = make_uint2(i, slot);
     for (uint32_t j = 0; j < ns; ++j)
         p.slices[(size_t)x * p.slice_cap + at + j] = make_uint4(i, j * kSumSlice, slot + j, 0u);
@@ -2275,8 +2272,11 @@ int plan_binned(const flashsca_value *v, ScaPlan *pl, ScaWork *w)
     // about 1.2 on the six-camera ring and 1.6 with eight cameras; a call
     // with more than twice its points takes the scatter form on the device.
     w->rec_cap = 2 * pts;
-    // full slices of every record, and some
-    w->slice_cap = w->rec_cap / kSumSlice + 64;
+    // Slices: bins of n > kSumSlice records have ceil(n / kSumSlice) <=
+    // (n + kSumSlice - 1) / kSumSlice each, their records together fit
+    // rec_cap, and there are at most rec_cap / (kSumSlice + 1) such bins.
+    const uint64_t multi_max = nb < w->rec_cap / (kSumSlice + 1) ? nb : w->rec_cap / (kSumSlice + 1);
+    w->slice_cap = (w->rec_cap + (kSumSlice - 1) * multi_max) / kSumSlice + 1;
     int32_t at = 0;
     for (int l = 0; l < p.L; ++l) {
         p.level_bin0[l] = at;

@@ -52,7 +52,8 @@ def run(fb, inst, g, device, dtype=None, want=("value", "offsets", "logits")):
         ctypes.c_uint64(need.value), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert rc == 0, fb.status_string(rc)
     torch.cuda.synchronize()
-    misc = ws[:16].view(torch.int32).cpu().numpy()   # records, -, scattered tiles, full
+    # records, -, scattered tiles, full, slices, bins in slices
+    misc = ws[:24].view(torch.int32).cpu().numpy()
     return {k: (t if k in want else None) for k, t in out.items()}, misc
 
 
@@ -79,6 +80,7 @@ def check(fb, inst, device, what, full=False, scattered=None, half=False):
         tol = K * 2.0 ** -24 * ref["value_scale"] * 1.01 + u * np.abs(ref["value"]) * 1.01 + tiny
         assert np.all(np.abs(a - ref["value"]) <= tol)
         assert np.array_equal(h["offsets"].cpu().numpy(), out["offsets"].cpu().numpy())
+    return misc
 
 
 @pytest.mark.parametrize("D", [8, 16, 24, 32, 48, 64])
@@ -164,3 +166,22 @@ def test_binned_large_call_is_the_default(fb, device):
     assert_bwd_parity({k: t.cpu().numpy() for k, t in a.items()}, ref, wl, "auto")
     b = fb.sca_backward(*args, method="scatter")
     assert_bwd_parity({k: t.cpu().numpy() for k, t in b.items()}, ref, wl, "scatter")
+
+
+def test_binned_slices_of_bins_barely_above_a_slice(fb, device):
+    """Bins of about 1100 records take two slices of 1024 each: the workspace
+    has the slots for all of them, and the call is not left to the scatter
+    form."""
+    inst = small(28, B=1, N=1, levels=((70, 105),), C=64, heads=8, P=32, Z=4, X=64, Y=64, x_min=2.0,
+                 dx=0.25, y_min=-2.0, dy=0.0625)
+    wl = inst.wl
+    # one wide camera along x sees every query near the middle of the image,
+    # and the points lie evenly over the map around it: 1114 a bin
+    inst.lidar2img[0, 0] = np.array([[wl.img_w / 2, -1, 0, 0], [wl.img_h / 2, 0, -1, 0], [1, 0, 0, 0],
+                                     [0, 0, 0, 1]], np.float32)
+    h, w = wl.levels[0]
+    rng = np.random.default_rng(28)
+    inst.offsets[...] = (rng.uniform(-0.5, 0.5, inst.offsets.shape) * (w, h)).astype(np.float32)
+    misc = check(fb, inst, device, "two slices a bin")
+    pts = wl.B * wl.Q * wl.heads * wl.L * wl.P
+    assert misc[4] > 2 * pts // 1024 + 64   # more than full slices of the most records there can be
