@@ -154,8 +154,10 @@ def test_sca_forward_replays(fb, device):
                                                          (2, 4), (1, 2), (1, 1), (5, 3)),
                                          X=4, Y=3)],
                          ids=["default", "lds-above-64k"])
-def test_sca_backward_replays(fb, device, kw):
-    """The fill and the scatter kernel in one graph; the second case needs
+@pytest.mark.parametrize("method", tsb.METHODS)
+def test_sca_backward_replays(fb, device, kw, method):
+    """The scatter form's fill and kernel, or the binned form's kernels with
+    the workspace that the call allocates, in one graph; the second case needs
     more than 64 KiB of LDS, so its launch raises the kernel's LDS limit."""
     import torch
     insts = _sca_instances(REPLAYS + 1, **kw)
@@ -166,13 +168,13 @@ def test_sca_backward_replays(fb, device, kw):
                 grad_offsets=torch.empty(tuple(off.shape), device=device),
                 grad_logits=torch.empty(tuple(lg.shape), device=device))
     args = (insts[0].z, fb.grid_of(wl), (wl.img_h, wl.img_w), wl.levels, wl.heads)
-    fb.sca_backward(v, l2i, *args, off, lg, g, **outs)
+    fb.sca_backward(v, l2i, *args, off, lg, g, **outs, method=method)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        fb.sca_backward(v, l2i, *args, off, lg, g, **outs)
+        fb.sca_backward(v, l2i, *args, off, lg, g, **outs, method=method)
     for k, inst in enumerate(insts[1:]):
-        print(f"[case] sca backward graph replay {k} cfg_id={inst.wl.cfg_id}", flush=True)
+        print(f"[case] sca backward {method} graph replay {k} cfg_id={inst.wl.cfg_id}", flush=True)
         for dst, src in zip((v, l2i, off, lg), ts._dev(inst, device)):
             dst.copy_(src)
         gnew = tsb._g(inst.wl)

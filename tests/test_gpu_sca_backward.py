@@ -15,6 +15,10 @@ of |terms|):
     d a_j.
 Elements the oracle gives no term must be exactly zero.  All calls go
 through the C ABI via the thin binding.
+
+The tile orders, the row merge and the full-size calls are tested in both
+forms: by default a call of many points takes the binned one, and the scatter
+form's kernel also serves the tiles that the binned form leaves.
 """
 import numpy as np
 import pytest
@@ -25,6 +29,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 U = 2.0 ** -24
+METHODS = ("binned", "scatter")
 
 
 @pytest.fixture(scope="module")
@@ -49,7 +54,7 @@ def _dev(inst, device):
 
 
 def gpu_bwd(fb, inst, g, device, reduce="mean", want=("value", "offsets", "logits"),
-            prefill=None):
+            prefill=None, method="auto"):
     import torch
     wl = inst.wl
     v, l2i, off, lg = _dev(inst, device)
@@ -60,7 +65,7 @@ def gpu_bwd(fb, inst, g, device, reduce="mean", want=("value", "offsets", "logit
                   grad_logits=torch.full(tuple(lg.shape), prefill, device=device))
     r = fb.sca_backward(v, l2i, inst.z, fb.grid_of(wl), (wl.img_h, wl.img_w), wl.levels,
                         wl.heads, off, lg, torch.from_numpy(g).to(device), want=want,
-                        reduce=reduce, **kw)
+                        reduce=reduce, method=method, **kw)
     torch.cuda.synchronize()
     return {k: (t.cpu().numpy() if t is not None else None) for k, t in r.items()}
 
@@ -93,12 +98,12 @@ def assert_bwd_parity(gpu, ref, wl, what=""):
 
 
 def check(fb, inst, device, reduce="mean", what="", want=("value", "offsets", "logits"),
-          prefill=None):
+          prefill=None, method="auto"):
     wl = inst.wl
-    print(f"[case] sca backward {what} value={inst.value.shape} {wl.dtype} heads={wl.heads} "
+    print(f"[case] sca backward {method} {what} value={inst.value.shape} {wl.dtype} heads={wl.heads} "
           f"P={wl.P} Z={wl.Z} X={wl.X} Y={wl.Y} reduce={reduce} want={want}", flush=True)
     g = _g(wl)
-    gpu = gpu_bwd(fb, inst, g, device, reduce, want, prefill)
+    gpu = gpu_bwd(fb, inst, g, device, reduce, want, prefill, method)
     ref = oracle.sca_backward_instance(inst, g, reduce)
     for k in ("value", "offsets", "logits"):
         if k not in want:
@@ -132,21 +137,24 @@ def test_sca_backward_channel_and_head_shapes(fb, device, C, heads, dtype):
           what=f"C={C} heads={heads} {dtype}")
 
 
+@pytest.mark.parametrize("method", METHODS)
 @pytest.mark.parametrize("C,heads,dtype", [(256, 8, "f32"), (512, 16, "f32"), (256, 8, "bf16")])
-def test_sca_backward_head_to_xcd_order(fb, device, C, heads, dtype):
+def test_sca_backward_head_to_xcd_order(fb, device, C, heads, dtype, method):
     # heads a multiple of 8 and more than 32 points per head: tiles follow the
     # head-to-XCD order (two head groups at 16 heads, both batch elements)
     check(fb, small(5, C=C, heads=heads, dtype=dtype, P=16, Z=4, X=23, Y=19), device,
-          what=f"head order C={C} heads={heads} {dtype} P=16")
+          what=f"head order C={C} heads={heads} {dtype} P=16", method=method)
 
 
+@pytest.mark.parametrize("method", METHODS)
 @pytest.mark.parametrize("C,heads,P", [(256, 8, 8), (256, 8, 16), (32, 4, 16)])
-def test_sca_backward_azimuth_block_order(fb, device, C, heads, P):
+def test_sca_backward_azimuth_block_order(fb, device, C, heads, P, method):
     # a 32 x 48 grid of six whole 16 x 16 blocks: rank order at P = 8 (24
     # points per head), the azimuth order of the blocks at P = 16 (with the
     # head order at 8 heads, the band order at 4)
     check(fb, small(6, C=C, heads=heads, P=P, Z=4, X=32, Y=48, x_min=-30.0, dx=2.0, y_min=-45.0,
-                    dy=2.0), device, what=f"azimuth order C={C} heads={heads} P={P}", prefill=np.nan)
+                    dy=2.0), device, what=f"azimuth order C={C} heads={heads} P={P}", prefill=np.nan,
+          method=method)
 
 
 @pytest.mark.parametrize("P,Z,L", [(1, 1, 1), (3, 1, 2), (8, 4, 4), (32, 4, 4), (64, 8, 8)])
@@ -177,8 +185,9 @@ def test_sca_backward_degenerate_inputs(fb, device):
     assert np.all(gpu["offsets"] == 0.0) and np.all(gpu["logits"] == 0.0)
 
 
+@pytest.mark.parametrize("method", METHODS)
 @pytest.mark.parametrize("case", ["spread", "crowded"])
-def test_sca_backward_row_merge_extremes(fb, device, case):
+def test_sca_backward_row_merge_extremes(fb, device, case, method):
     """The value gradient's row merge at its extremes.  `spread`: offsets
     uniform over a 116 x 200 map, so nearly every in-range (point, slot, tap)
     row of a tile's chunk is a distinct pixel: about as many keys as rows in
@@ -191,19 +200,20 @@ def test_sca_backward_row_merge_extremes(fb, device, case):
         inst.offsets[...] = rng.uniform(-150.0, 150.0, inst.offsets.shape).astype(np.float32)
     else:
         inst = small(11, levels=((4, 4),), C=256, heads=8, P=8, Z=4, X=16, Y=16)
-    check(fb, inst, device, what=f"row merge {case}")
+    check(fb, inst, device, what=f"row merge {case}", method=method)
 
 
+@pytest.mark.parametrize("method", METHODS)
 @pytest.mark.parametrize("name,P", [("sca_base", 8), ("sca_base", 16), ("sca_base", 32),
                                     ("sca_base_bf16", 8)])
-def test_sca_backward_bevformer_base(fb, device, name, P):
+def test_sca_backward_bevformer_base(fb, device, name, P, method):
     """Table 7's setting at every P the bench times (the row merge's keys and
     member lists grow with P), and the bfloat16 batch of two; every element
     of all three gradients checked against the oracle."""
     wl = synth.sca_config(name).with_(P=P)
     print(f"[case] {name} P={P} B={wl.B} dtype={wl.dtype}", flush=True)
     inst = synth.make_sca_workload(wl)
-    check(fb, inst, device, what=f"{name} P={P}")
+    check(fb, inst, device, what=f"{name} P={P}", method=method)
 
 
 def test_sca_backward_adjoint_of_gpu_forward(fb, device):
@@ -227,7 +237,8 @@ def test_sca_backward_adjoint_of_gpu_forward(fb, device):
         assert abs(lhs - rhs) <= 1e-5 * bound
 
 
-def test_sca_backward_on_side_stream(fb, device):
+@pytest.mark.parametrize("method", METHODS)
+def test_sca_backward_on_side_stream(fb, device, method):
     import torch
     inst = small(9)
     wl = inst.wl
@@ -238,7 +249,7 @@ def test_sca_backward_on_side_stream(fb, device):
     torch.cuda.synchronize()
     with torch.cuda.stream(s):
         r = fb.sca_backward(v, l2i, inst.z, fb.grid_of(wl), (wl.img_h, wl.img_w), wl.levels,
-                            wl.heads, off, lg, gt, stream=s)
+                            wl.heads, off, lg, gt, stream=s, method=method)
     s.synchronize()
     gpu = {k: t.cpu().numpy() for k, t in r.items()}
     assert_bwd_parity(gpu, oracle.sca_backward_instance(inst, g), wl, "side stream")
@@ -262,7 +273,8 @@ def test_sca_backward_allocates_nothing_beyond_its_outputs(fb, device):
     assert torch.cuda.max_memory_allocated(device) == base
 
 
-def test_prepared_sca_backward_matches_oracle(fb, device):
+@pytest.mark.parametrize("method", METHODS)
+def test_prepared_sca_backward_matches_oracle(fb, device, method):
     import torch
     inst = small(11)
     wl = inst.wl
@@ -273,7 +285,8 @@ def test_prepared_sca_backward_matches_oracle(fb, device):
     go = torch.full(tuple(off.shape), float("nan"), device=device)
     gl = torch.full(tuple(lg.shape), float("nan"), device=device)
     call = fb.prepare_sca_backward(v, l2i, inst.z, fb.grid_of(wl), (wl.img_h, wl.img_w),
-                                   wl.levels, wl.heads, off, lg, gt, gv, go, gl)
+                                   wl.levels, wl.heads, off, lg, gt, gv, go, gl,
+                                   method=method)
     call()
     call()
     torch.cuda.synchronize()

@@ -2,9 +2,10 @@
 with the bars of test_gpu_sca_backward (the value gradient's covers float32
 addition in any order).  The shapes are those where the form can go wrong:
 each head width it serves, maps whose sides are on, above and below the bin
-size (7 x 7 pixels), levels summed by a wavefront and by a workgroup, points
-spread over more bins than a tile's table holds, and more records than the
-workspace does.  A 16-bit value gradient must be the float32 one rounded once.
+size (7 x 7 pixels), bins summed whole and in slices, points spread over more
+bins than a tile's table holds, more records than the workspace does, and
+output gradients that are not finite.  A 16-bit value gradient must be the
+float32 one rounded once.
 """
 import numpy as np
 import pytest
@@ -101,12 +102,20 @@ def test_binned_map_edges(fb, device, levels):
     check(fb, inst, device, f"edges {levels}")
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_binned_shared_bins(fb, device, dtype):
-    # bins of several rounds of records each, summed by a whole workgroup
-    inst = small(22, levels=((5, 11), (20, 44)), C=64, heads=2, dtype=dtype, P=32, Z=4, X=48,
+def crowded(seed, D=32, dtype="f32"):
+    """Bins of several slices of records each."""
+    return small(seed, levels=((5, 11), (20, 44)), C=2 * D, heads=2, dtype=dtype, P=32, Z=4, X=48,
                  Y=40, dx=1.0, dy=1.0)
-    check(fb, inst, device, f"shared bins {dtype}", half=dtype == "bf16")
+
+
+@pytest.mark.parametrize("D,dtype", [(32, "f32"), (32, "bf16"), (8, "f32"), (16, "f16"), (24, "f32"),
+                                     (48, "bf16"), (64, "f32")])
+def test_binned_shared_bins(fb, device, D, dtype):
+    # slices summed by a wavefront each and joined: one channel slice (8 to 32
+    # channels) and two (48 and 64)
+    misc = check(fb, crowded(22, D, dtype), device, f"shared bins D={D} {dtype}",
+                 half=dtype != "f32")
+    assert misc[4] > misc[5] > 0   # slices, bins in slices
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
@@ -141,6 +150,42 @@ def test_binned_degenerate_inputs(fb, device):
     inst.offsets[:, : inst.wl.Q // 2] = 1e9
     inst.offsets[:, inst.wl.Q // 2:, :, :, ::2] = np.nan
     check(fb, inst, device, "far and NaN offsets")
+
+
+@pytest.mark.parametrize("case,D,dtype", [("whole", 8, "f32"), ("whole", 32, "bf16"),
+                                          ("whole", 48, "f32"), ("slices", 24, "f32"),
+                                          ("slices", 32, "f32"), ("slices", 64, "f16")])
+def test_binned_gradient_that_is_not_finite(fb, device, case, D, dtype):
+    """Infinite and NaN elements of the output gradient reach the elements that
+    their points touch, and no other (the matrix rows multiply them by the zero
+    weights of every pixel near by)."""
+    import torch
+
+    inst = crowded(29, D, dtype) if case == "slices" else small(29, C=4 * D, heads=4, dtype=dtype)
+    wl = inst.wl
+    print(f"[case] sca binned not finite {case} D={D} {dtype}", flush=True)
+    g = _g(wl)
+    # single elements of a few queries that a camera sees
+    seen = np.argwhere(oracle.sca_backward_instance(inst, np.ones_like(g))["point_terms"]
+                       .reshape(wl.B, wl.Q, -1).sum(-1) > 0)
+    rng = np.random.default_rng(29)
+    bad = np.zeros_like(g)
+    for k, (b, q) in enumerate(seen[rng.choice(len(seen), 3, replace=False)]):
+        bad[b, q, rng.integers(wl.C)] = (np.inf, -np.inf, np.nan)[k]
+    rest = np.where(bad == 0, g, np.float32(0))
+    touched = oracle.sca_backward_instance(inst, (bad != 0).astype(np.float32))["value_scale"] > 0
+    assert touched.any() and not touched.all()
+    ref = oracle.sca_backward_instance(inst, rest)
+    for dt in {torch.float32, synth.to_storage(inst.value[:1], dtype).dtype}:
+        out, misc = run(fb, inst, np.where(bad == 0, g, bad), device, dt)
+        assert (misc[4] > 0) == (case == "slices")
+        v = out["value"].float().cpu().numpy()
+        assert not np.isfinite(v[touched]).any()
+        v[touched] = ref["value"][touched]
+        if dt == torch.float32:
+            assert_bwd_parity({"value": v}, ref, wl, f"not finite {case} D={D}")
+        else:
+            assert np.isfinite(v).all()
 
 
 def test_binned_large_call_is_the_default(fb, device):
