@@ -312,6 +312,18 @@ int flashbev_launch_info(const flashbev_features *features, const flashbev_bev_g
                          int32_t *threads_per_workgroup, int32_t *lds_bytes,
                          int32_t *cells_per_wave, int32_t *lanes_per_cell);
 
+/*
+ * The projection phase flashbev_sample_vt takes for these arguments (written to
+ * *path), with the checks of flashbev_launch_info and no HIP call.  The results
+ * differ in rounding at most: merged heights sum the weights of a shared tap
+ * before the product with the feature.
+ */
+#define FLASHBEV_PATH_PER_CELL 0   /* passes of one cell each */
+#define FLASHBEV_PATH_CULLED   1   /* cameras culled per group of cells, packed passes */
+#define FLASHBEV_PATH_MERGED   2   /* the same; heights on the same taps are one record */
+int flashbev_launch_path(const flashbev_features *features, const flashbev_bev_grid_spec *spec,
+                         const flashbev_z_bins *z_bins, int32_t *path);
+
 #ifdef __cplusplus
 }
 #endif

@@ -628,6 +628,21 @@ def launch_info(shape, dtype: str, z_bins, grid: BevGrid, img_hw, reduce: str = 
             "cells_per_wave": cpw.value, "lanes_per_cell": lpc.value}
 
 
+FORWARD_PATHS = ("per cell", "culled", "merged")
+
+
+def launch_path(shape, dtype: str, z_bins, grid: BevGrid, img_hw, reduce: str = "mean",
+                data_ptr: int = 0) -> str:
+    """The projection phase of the forward for these arguments (no HIP call)."""
+    z = _z_array(z_bins)
+    f, g, zb = _packed(shape, DTYPE_CODES[dtype], data_ptr, img_hw, grid, z, reduce)
+    path = ctypes.c_int32()
+    rc = _packed_call("flashbev_launch_path", "PPPP")(f, g, zb, ctypes.byref(path))
+    if rc != 0:
+        raise FlashBevError(rc, "flashbev_launch_path")
+    return FORWARD_PATHS[path.value]
+
+
 def grid_of(wl) -> BevGrid:
     """BevGrid of a workload description with x_min/dx/X/y_min/dy/Y fields."""
     return BevGrid(wl.x_min, wl.dx, wl.X, wl.y_min, wl.dy, wl.Y, wl.depth_eps)

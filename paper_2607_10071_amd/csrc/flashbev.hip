@@ -281,7 +281,11 @@ enum PhaseSlot {
 #endif
 
 // projection phases of the forward (sample_vt_fwd)
-enum FwdPath { kPerCell, kCulled, kMerged };
+enum FwdPath {
+    kPerCell = FLASHBEV_PATH_PER_CELL,
+    kCulled = FLASHBEV_PATH_CULLED,
+    kMerged = FLASHBEV_PATH_MERGED
+};
 
 template <int DT, int LW, int VPL, int PATH>
 struct FwdWaves {
@@ -2935,6 +2939,17 @@ int flashbev_launch_info(const flashbev_features *features, const flashbev_bev_g
     if (lds_bytes) *lds_bytes = (int32_t)pl.lds;
     if (cells_per_wave) *cells_per_wave = pl.prm.cpw;
     if (lanes_per_cell) *lanes_per_cell = pl.prm.lpc;
+    return FLASHBEV_OK;
+}
+
+int flashbev_launch_path(const flashbev_features *features, const flashbev_bev_grid_spec *spec,
+                         const flashbev_z_bins *z_bins, int32_t *path)
+{
+    if (!path) return FLASHBEV_ERR_NULLPTR;
+    Plan pl;
+    const int rc = make_plan(features, nullptr, spec, z_bins, nullptr, false, &pl);
+    if (rc) return rc;
+    *path = pl.path;
     return FLASHBEV_OK;
 }
 

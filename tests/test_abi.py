@@ -459,3 +459,24 @@ def test_autograd_wrappers_are_exported_and_refuse_host_tensors():
     grid = fb.BevGrid(x_min=-1.0, dx=1.0, X=2, y_min=-1.0, dy=1.0, Y=2)
     with pytest.raises(ValueError):
         fb.sample_vt_autograd(feats, l2i, [0.0], grid, (8, 8))
+
+
+@pytest.mark.parametrize("kw,path", [
+    (dict(), "per cell"),                                   # three cells a group, one pass a cell
+    (dict(shape=(1, 6, 32, 88, 32)), "culled"),             # eight cells a group
+    (dict(Z=16), "culled"),                                 # sparse heights, several passes a cell
+    (dict(Z=64), "merged"),
+    (dict(Z=64, XY=(50, 50)), "culled"),                    # too few wavefronts
+    (dict(Z=64, nan=True), "culled"),                       # no spacing to go by
+])
+def test_forward_projection_phase(kw, path):
+    shape = kw.get("shape", (1, 6, 32, 88, 80))
+    X, Y = kw.get("XY", (200, 200))
+    grid = fb.BevGrid(-50, 100 / X, X, -50, 100 / Y, Y)
+    z = np.linspace(-4.5, 2.5, kw.get("Z", 8)).astype(np.float32)
+    if kw.get("nan"):
+        z[3] = np.nan
+    assert fb.launch_path(shape, "f32", z, grid, (256, 704)) == path
+    with pytest.raises(fb.FlashBevError):
+        fb.launch_path((1, 65, 32, 88, 80), "f32", z, grid, (256, 704))
+    assert fb._lib().flashbev_launch_path(None, None, None, None) == S["ERR_NULLPTR"]

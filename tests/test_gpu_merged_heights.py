@@ -1,15 +1,17 @@
 """GPU parity of the forward where consecutive heights share their taps and
-are merged into one record: dense heights in any order, repeated and
-non-finite heights, passes of several height chunks and of several cells, maps
-of one row or column, ragged grids and every storage type, against the CPU
-oracle with test_gpu_parity's bars.  The grids have the cell groups from which
-merging is taken (2048), and spacings well below it.
+are merged into one record: dense heights in any order, repeated heights,
+passes of several height chunks and of several cells, maps of one row or
+column, ragged grids and every storage type, against the CPU oracle with
+test_gpu_parity's bars.  The grids have the cell groups from which merging is
+taken (2048), and spacings well below it; each test asserts that it is taken
+(non-finite heights, whose spacing says nothing, go without).
 """
 import numpy as np
 import pytest
 
 import synth
-from test_gpu_parity import check_instance, small
+import test_gpu_parity as tp
+from test_gpu_parity import small
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +20,13 @@ pytestmark = pytest.mark.gpu
 def fb():
     import paper_2607_10071_amd as m
     return m
+
+
+def check_instance(fb, inst, device, reduce="mean", what="", path="merged"):
+    wl = inst.wl
+    assert fb.launch_path(inst.features.shape, wl.dtype, inst.z, fb.grid_of(wl),
+                          (wl.img_h, wl.img_w), reduce) == path
+    tp.check_instance(fb, inst, device, reduce, what)
 
 
 @pytest.mark.parametrize("dtype,C", [("f32", 16), ("f32", 32), ("f32", 80), ("bf16", 64), ("f16", 33),
@@ -44,7 +53,8 @@ def test_height_orders(fb, device, order):
     else:
         z[7], z[20] = np.nan, np.inf
     inst.z = np.ascontiguousarray(z.astype(np.float32))
-    check_instance(fb, inst, device, what=order)
+    check_instance(fb, inst, device, what=order,
+                   path="culled" if order == "nonfinite" else "merged")
 
 
 @pytest.mark.parametrize("H,W", [(1, 44), (16, 1), (1, 1), (2, 2)])
