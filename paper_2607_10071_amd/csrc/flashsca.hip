@@ -108,6 +108,7 @@ constexpr int kBinW = 7, kBinH = 7, kBinRows = kBinH + 1;
 constexpr int kBinPix = kBinW * kBinH;
 // a tile's distinct bins: an open-addressing table in LDS, kept at most 7/8 full
 constexpr int kTabRows = 1024, kTabMax = 896, kTabShift = 32 - 10;
+constexpr int kTabProbes = 256;   // a bin that finds no row in as many gives the table up
 constexpr uint32_t kTabBytes = (2u * kTabRows + 3u * FLASHSCA_LMAX + 4u) * 4u;
 constexpr uint32_t kTabEmpty = 0xFFFFFFFFu;
 constexpr uint32_t kTileScatter = 0xFFFFFFFFu;   // tile_n of a tile left to the scatter kernel
@@ -1143,7 +1144,7 @@ __global__ void __launch_bounds__(kScaBwdThreads) sca_bin_count(const ScaParams 
             if (!sca_locate(p, m, m.ref + (size_t)(s.qi * p.N + n) * p.Z, s, j, c)) continue;
             sca_point_bins(p, t, c, n, [&](uint32_t key, int, int) {
                 uint32_t h = sca_tab_hash(key);
-                for (int probe = 0; probe < kTabRows; ++probe) {
+                for (int probe = 0; probe < kTabProbes; ++probe) {
                     uint32_t old = t.key[h];
                     if (old == kTabEmpty) old = atomicCAS(&t.key[h], kTabEmpty, key);
                     if (old == kTabEmpty && atomicAdd(&t.n[0], 1u) >= (uint32_t)kTabMax)
@@ -1157,6 +1158,10 @@ __global__ void __launch_bounds__(kScaBwdThreads) sca_bin_count(const ScaParams 
                 t.n[1] = 1u;
             });
         }
+        // A tile of too many bins is left to the scatter kernel, and its table
+        // given up: points would go on to probe full rows (2 x 1035 queries, 10
+        // cameras, 128 points per query and head on wide maps took 14.7 ms).
+        if (*(volatile uint32_t *)&t.n[1]) break;
     }
     __syncthreads();
     const uint32_t tile = sca_tile_id(p, tl);
