@@ -161,9 +161,10 @@ int flashsca_backward(const flashsca_value *value, const float *lidar2img,
  * The same backward in binned form, on a caller workspace.  The points are
  * grouped by the pixels they touch and every element of the value gradient is
  * summed and written once, without float atomics (a call whose points exceed
- * the workspace's records, more than two per point, and a group of queries
- * whose points spread over very many pixel bins are scattered as in
- * flashsca_backward, decided on the device).
+ * the workspace's records, more than two per point with up to eight cameras
+ * and N / 4 with more, and a group of queries whose points spread over very
+ * many pixel bins are scattered as in flashsca_backward, decided on the
+ * device).
  *
  *   grad_value         as in flashsca_backward, but in `grad_value_dtype`:
  *                      FLASHBEV_F32, or the value's dtype (the float32 sum

@@ -2274,9 +2274,10 @@ int plan_binned(const flashsca_value *v, ScaPlan *pl, ScaWork *w)
     if (nb > (1ull << 26) || pts > (1ull << 28) || w->tiles > (1ull << 22))
         return FLASHBEV_ERR_UNSUPPORTED;
     // Records: a point has one per hit camera and bin its footprint touches,
-    // about 1.2 on the six-camera ring and 1.6 with eight cameras; a call
-    // with more than twice its points takes the scatter form on the device.
-    w->rec_cap = 2 * pts;
+    // about 1.2 on a ring of six cameras, 1.6 on one of eight and so on in
+    // proportion; a call with more (2 a point up to eight cameras) takes the
+    // scatter form on the device.
+    w->rec_cap = pts * (uint64_t)(p.N > 8 ? p.N : 8) / 4;
     // Slices: bins of n > kSumSlice records have ceil(n / kSumSlice) <=
     // (n + kSumSlice - 1) / kSumSlice each, their records together fit
     // rec_cap, and there are at most rec_cap / (kSumSlice + 1) such bins.

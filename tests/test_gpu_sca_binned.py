@@ -166,6 +166,15 @@ def test_binned_more_records_than_workspace(fb, device, dtype):
     check(fb, inst, device, f"full {dtype}", full=True, half=dtype == "bf16")
 
 
+def test_binned_room_for_many_cameras(fb, device):
+    # a ring of 24 cameras: more than two records per point
+    inst = small(31, B=1, N=24, levels=((32, 88),), C=64, heads=2, P=4, Z=4, X=40, Y=36, x_min=-40.0,
+                 dx=2.0, y_min=-36.0, dy=2.0)
+    wl = inst.wl
+    misc = check(fb, inst, device, "24 cameras")
+    assert misc[0] > 2 * wl.B * wl.Q * wl.heads * wl.L * wl.P
+
+
 def test_binned_points_without_value_gradient(fb, device):
     inst = small(25, C=64, heads=2)
     g = _g(inst.wl)
