@@ -177,7 +177,8 @@ int flashsca_backward(const flashsca_value *value, const float *lidar2img,
  * FLASHBEV_ERR_UNSUPPORTED where the binned form does not serve the shape
  * (head rows other than 8, 16, 24, 32, 48 or 64 channels, an empty output, no
  * cameras, or more than 2^28 points); FLASHBEV_ERR_SCRATCH for a workspace
- * that is too small.  The scatter form is the faster one for few points.
+ * that is too small.  flashsca_backward_workspace_best says where this form is
+ * the faster one.
  */
 int flashsca_backward_ws(const flashsca_value *value, const float *lidar2img,
                          const flashbev_bev_grid_spec *spec, const flashbev_z_bins *anchors,
@@ -185,6 +186,18 @@ int flashsca_backward_ws(const flashsca_value *value, const float *lidar2img,
                          const float *grad_out, void *grad_value, int32_t grad_value_dtype,
                          float *grad_offsets, float *grad_logits, void *workspace,
                          uint64_t workspace_bytes, void *stream);
+
+/*
+ * Workspace bytes with which the backward with a value gradient of
+ * `grad_value_dtype` runs fastest: those of flashsca_backward_ws, or 0 where
+ * flashsca_backward is the only form or expected to be the faster one (few
+ * points, few of them per query and head, narrow heads, small maps); no HIP
+ * call.
+ */
+int flashsca_backward_workspace_best(const flashsca_value *value,
+                                     const flashbev_bev_grid_spec *spec,
+                                     const flashbev_z_bins *anchors, int32_t P,
+                                     int32_t grad_value_dtype, uint64_t *bytes);
 
 /* Workspace bytes of flashsca_backward_ws for these arguments; no HIP call. */
 int flashsca_backward_workspace_size(const flashsca_value *value,

@@ -939,28 +939,32 @@ def _sca_bwd_outputs(value, Q, heads, L, P, grad_value, grad_offsets, grad_logit
 
 
 SCA_BACKWARD_METHODS = ("auto", "binned", "scatter")
-# Points (B X Y heads L P) from which "auto" takes the binned form: its six
-# launches cost more than the scatter form's atomics below (MI355X, scatter /
-# binned us: 160,000 points 61 / 68; 320,000 124 / 108; 2,560,000 563 / 416;
-# 10,240,000 1450 / 1060).
+# Points (B X Y heads L P) below which "auto" takes the scatter form at any
+# shape; from them on flashsca_backward_workspace_best decides.
 SCA_BINNED_MIN_POINTS = 1 << 18
 
 
-def _sca_workspace_bytes(v, g, zb, P: int, method: str, points: int, grad_value) -> int:
+def _sca_workspace_bytes(v, g, zb, P: int, method: str, points: int, grad_value,
+                         grad_dtype: int = 0) -> int:
     """Workspace bytes of the binned backward, or -1 where flashsca_backward
     is taken: for calls that want no value gradient (which has nothing to bin;
-    both forms are one kernel there), with "auto" for few points, and for
-    shapes that the binned form does not serve."""
+    both forms are one kernel there), with "auto" where it is the faster form
+    for a value gradient of the type ``grad_dtype`` (a code), and for shapes
+    that the binned form does not serve."""
     if method not in SCA_BACKWARD_METHODS:
         raise ValueError(f"method must be one of {SCA_BACKWARD_METHODS}")
     if method == "scatter" or grad_value is None or (method == "auto"
                                                      and points < SCA_BINNED_MIN_POINTS):
         return -1
     out = ctypes.c_uint64()
+    if method == "auto":
+        rc = _packed_call("flashsca_backward_workspace_best", "PPPiiP")(v, g, zb, P, grad_dtype,
+                                                                       ctypes.byref(out))
+        return int(out.value) if rc == STATUS["OK"] and out.value else -1
     rc = _packed_call("flashsca_backward_workspace_size", "PPPiP")(v, g, zb, P, ctypes.byref(out))
     if rc == STATUS["OK"]:
         return int(out.value)
-    if method == "binned" and rc != STATUS["ERR_UNSUPPORTED"]:
+    if rc != STATUS["ERR_UNSUPPORTED"]:
         raise FlashBevError(rc, "flashsca_backward_workspace_size")
     return -1   # the scatter form's own checks report what is wrong
 
@@ -986,9 +990,9 @@ def sca_backward(value, lidar2img, anchors, grid: BevGrid, img_hw, levels, heads
     method   "binned" (flashsca_backward_ws: the points are grouped by pixel
              and the value gradient written once; it needs a device
              workspace, allocated here), "scatter" (flashsca_backward: float
-             atomics, no workspace) or "auto" (binned from
-             SCA_BINNED_MIN_POINTS points on).  The scatter form serves the
-             shapes the binned form does not.
+             atomics, no workspace) or "auto" (the form expected to be the
+             faster one for these sizes).  The scatter form serves the shapes
+             the binned form does not.
 
     Returns a dict with the float32 tensors ``value`` [B, N, S, C],
     ``offsets`` [B, X*Y, heads, L, P, 2] and ``logits`` [B, X*Y, heads, L, P]
@@ -1017,8 +1021,9 @@ def _sca_backward(value, lidar2img, anchors, grid, img_hw, levels, heads, offset
                       *(t for t in (grad_value, grad_offsets, grad_logits) if t is not None))
     s = _stream_handle(stream, dev)
     wants_value = grad_value is not None or "value" in want
-    need = _sca_workspace_bytes(v, g, zb, P, method, logits.numel(), wants_value or None)
     convert = value_dtype is not None and value_dtype != torch.float32 and wants_value
+    need = _sca_workspace_bytes(v, g, zb, P, method, logits.numel(), wants_value or None,
+                                _dtype_code(value) if convert else DTYPE_CODES["f32"])
     # the gradients first: where the device has no room left for a workspace,
     # the scatter form runs without one
     outs = _sca_bwd_outputs(value, Q, heads, len(levels), P, grad_value, grad_offsets,

@@ -2314,6 +2314,40 @@ int plan_binned(const flashsca_value *v, ScaPlan *pl, ScaWork *w)
     return FLASHBEV_OK;
 }
 
+// Whether the binned form is expected to be the faster one.  It costs a second
+// projection, six launches, and a table's work per tile and a wavefront's per
+// bin; what it saves are the scatter form's atomics and its row merge.  The
+// lines follow 520 calls drawn over sizes, maps, cameras, head widths and both
+// gradient types (2^18 points and more; MI355X, scatter / binned us):
+//   * What a tile saves grows with its points per query and head (LP), the head
+//     width and the cameras that see them; hardly with the call's size.  A
+//     16-bit gradient costs the scatter form a pass over float32 sums.  A fit of
+//     the times' ratio: 2 log2 LP + log2 D + 1.8 log2 N + log2(points) / 3.2 +
+//     (16 bits: 2) against 21.  6 cameras, D = 32, LP = 4 151 / 192, LP = 8
+//     on a 116 x 200 map 139 / 116; D = 8, LP = 8 63 / 92, LP = 32 292 / 242.
+//   * On maps of few bins (18: 17 x 39 pixels) the row merge finds the same few
+//     pixels: 8 x 22 at 2,560,000 points 244 / 276; up to 45 bins with
+//     few points per query, 703,872 points 120 / 142, with many 1,920,000 289 / 208.
+//   * Many bins of few points: BEVFormer's levels, four batch elements, 8 points
+//     per bin 321 / 429, 32 827 / 744; with a 16-bit gradient 653 / 503.
+//   * A coarse grid under wide maps spreads a tile's points over more bins than
+//     its table holds, and it is scattered after all (about from LP N bins =
+//     170 queries on: 1035 queries, LP = 128, 10 cameras 1304 / 2261; 1250
+//     queries, LP = 64, 6 cameras 578 / 820; but 1612 queries 651 / 442).
+// Over those calls the times are 1.31 times the scatter form's speed (binned
+// always: 1.28); the worst is 1.22 times slower than the scatter form (2.5).
+bool binned_pays(const ScaParams &p, int gv_dtype)
+{
+    const double pts = (double)p.B * p.Q * p.heads * p.LP;
+    const bool half = gv_dtype != FLASHBEV_F32;
+    if (pts < 262144.0 || p.bpc < 18) return false;
+    if (p.bpc < 45 && p.LP <= 16 && p.N <= 6 && pts < 800e3) return false;
+    if (!half && p.nbins > 50000 && pts < 16.0 * p.nbins) return false;
+    if ((double)p.LP * p.N * p.bpc > 170.0 * p.Q) return false;
+    return 2.0 * log2((double)p.LP) + log2((double)p.D) + 1.8 * log2((double)p.N) +
+               log2(pts) / 3.2 + (half ? 2.0 : 0.0) >= 21.0;
+}
+
 int launch_fn(ScaFn fn, ScaParams &p, uint64_t workgroups, int threads, size_t lds,
               hipStream_t st)
 {
@@ -2456,6 +2490,24 @@ extern "C" int flashsca_backward_workspace_size(const flashsca_value *value,
     rc = plan_binned(value, &pl, &w);
     if (rc) return rc;
     *bytes = w.total;
+    return FLASHBEV_OK;
+}
+
+extern "C" int flashsca_backward_workspace_best(const flashsca_value *value,
+                                                const flashbev_bev_grid_spec *spec,
+                                                const flashbev_z_bins *anchors, int32_t P,
+                                                int32_t grad_value_dtype, uint64_t *bytes)
+{
+    if (!bytes) return FLASHBEV_ERR_NULLPTR;
+    ScaPlan pl;
+    int rc = make_sca_plan(value, spec, anchors, P, ScaBufs{}, true, false, &pl);
+    if (rc) return rc;
+    if (grad_value_dtype != FLASHBEV_F32 && grad_value_dtype != value->dtype)
+        return FLASHBEV_ERR_DTYPE;
+    ScaWork w;
+    *bytes = 0;
+    if (plan_binned(value, &pl, &w) == FLASHBEV_OK && binned_pays(pl.prm, grad_value_dtype))
+        *bytes = w.total;
     return FLASHBEV_OK;
 }
 

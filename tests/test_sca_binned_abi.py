@@ -84,3 +84,50 @@ def test_python_method_argument():
     # nothing to bin without a value gradient: no workspace
     assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "binned", big, None) == -1
     assert fb._sca_workspace_bytes(*map(ctypes.byref, (v, g, zb)), 8, "binned", 1, True) == size()[1]
+
+
+def best(P=8, gv_dtype="f32", **kw):
+    v, g, zb, _z = structs(**kw)
+    out = ctypes.c_uint64()
+    rc = fb._lib().flashsca_backward_workspace_best(ctypes.byref(v), ctypes.byref(g),
+                                                    ctypes.byref(zb), P, fb.DTYPE_CODES[gv_dtype],
+                                                    ctypes.byref(out))
+    assert rc == S["OK"]
+    return out.value
+
+
+@pytest.mark.parametrize("kw,binned", [
+    (dict(), True),                                            # BEVFormer-base
+    (dict(X=32, Y=32), True), (dict(X=31, Y=32), False),       # from 2^18 points on
+    (dict(C=320), False),                                      # not served
+    (dict(N=12), True),
+    # points per query and head, head widths, cameras
+    (dict(levels=((116, 200),), P=4), False), (dict(levels=((116, 200),), P=8), True),
+    (dict(levels=((58, 100),), P=8, C=64), False), (dict(levels=((58, 100),), P=16, C=64), True),
+    (dict(levels=((58, 100),), P=8, C=64, dtype="bf16"), False),
+    (dict(levels=((58, 100),), P=8, C=64, dtype="bf16", gv_dtype="bf16"), True),
+    (dict(levels=((58, 100),), P=12, N=2), False), (dict(levels=((58, 100),), P=32, N=2), True),
+    # maps of few bins
+    (dict(levels=((14, 56),), P=32), False), (dict(levels=((17, 39),), P=32), True),
+    (dict(levels=((16, 44),), P=16, X=75, Y=80), False), (dict(levels=((16, 44),), P=16), True),
+    (dict(levels=((16, 44),), P=32, X=75, Y=80), True),
+    # points per bin
+    (dict(B=4, X=40, Y=40), False), (dict(B=4, X=64, Y=64), True),
+    (dict(B=4, X=40, Y=40, dtype="bf16"), False),              # a float32 gradient
+    (dict(B=4, X=40, Y=40, dtype="bf16", gv_dtype="bf16"), True),
+    # coarse grids under wide maps
+    (dict(P=32, X=40, Y=40), False), (dict(P=32, X=64, Y=64), True),
+])
+def test_where_the_binned_form_is_taken(kw, binned):
+    assert best(**kw) == (size(**{k: t for k, t in kw.items() if k != "gv_dtype"})[1] if binned
+                          else 0)
+
+
+def test_best_size_refuses_what_the_call_refuses():
+    v, g, zb, _z = structs()
+    out = ctypes.c_uint64()
+    call = fb._lib().flashsca_backward_workspace_best
+    ref = [ctypes.byref(t) for t in (v, g, zb)]
+    assert call(*ref, 8, fb.DTYPE_CODES["f32"], None) == S["ERR_NULLPTR"]
+    assert call(*ref, 8, fb.DTYPE_CODES["bf16"], ctypes.byref(out)) == S["ERR_DTYPE"]
+    assert call(*ref, 6, fb.DTYPE_CODES["f32"], ctypes.byref(out)) == S["ERR_SHAPE"]
