@@ -2356,13 +2356,16 @@ int make_plan(const flashbev_features *f, const float *l2i, const flashbev_bev_g
         // 200 x 200, C = 80 float32, 0.33 65 / 43, 0.17 123 / 52; but 50 x 50,
         // C = 32 float32 (312 wavefronts), 0.33 17.2 / 20.8.  Fewer than 16
         // heights have little to merge (202 x 306, 10 heights, 0.26 28.3 /
-        // 28.7).
+        // 28.7), and rows of at most 12 bytes little to load: they want twice
+        // the wavefronts (C = 3 float32, 2581 of them 17.1 / 21.9; 2 half,
+        // 3570 26.7 / 31.9; 4 half, 4776 49.0 / 39.2).
         double step = 0.0;
         for (int k = 1; k < zb->Z; ++k) step += fabs((double)zb->z[k] - (double)zb->z[k - 1]);
         const double ex = fabs((double)s->dx) * s->X, ey = fabs((double)s->dy) * s->Y;
         const double half = 0.5 * (ex > ey ? ex : ey);
         merge = zb->Z >= 16 && 0.75 * f->W * step / (zb->Z - 1) <= 0.45 * half &&
-                size_prod({(uint64_t)f->B, XY}) >= (uint64_t)cpw * kMergeWavesMin;
+                size_prod({(uint64_t)f->B, XY}) >=
+                    (uint64_t)cpw * kMergeWavesMin * (row <= 12 ? 2 : 1);
     }
     p.rcp_y = 1.0 / (double)(s->Y > 0 ? s->Y : 1);
     p.rcp_tiles = 1.0 / (double)(p.tiles_per_b > 0 ? p.tiles_per_b : 1);

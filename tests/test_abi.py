@@ -468,6 +468,9 @@ def test_autograd_wrappers_are_exported_and_refuse_host_tensors():
     (dict(Z=64), "merged"),
     (dict(Z=64, XY=(50, 50)), "culled"),                    # too few wavefronts
     (dict(Z=64, nan=True), "culled"),                       # no spacing to go by
+    (dict(Z=64, shape=(1, 6, 32, 88, 3)), "merged"),        # 5000 wavefronts, rows of 12 bytes
+    (dict(Z=64, shape=(1, 6, 32, 88, 3), XY=(160, 160)), "culled"),   # 3200
+    (dict(Z=64, shape=(1, 6, 32, 88, 4), XY=(160, 160)), "merged"),
 ])
 def test_forward_projection_phase(kw, path):
     shape = kw.get("shape", (1, 6, 32, 88, 80))
