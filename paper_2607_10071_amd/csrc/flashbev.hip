@@ -2343,9 +2343,10 @@ int make_plan(const flashbev_features *f, const float *l2i, const flashbev_bev_g
         // a non-finite height: no culling (the test's margins assume finite ends)
         if (!finite(lo) || !finite(hi)) p.cull = 0;
         // Merged records pay where consecutive heights mostly share their
-        // taps.  A camera with a focal length of about 3/4 of its image width
-        // sees heights `step` apart 0.75 W step / r feature pixels apart at
-        // range r; taken where that is at most 0.45 at half the grid's larger
+        // taps.  The matrices are on the device, so a focal length is assumed:
+        // 3/4 of the image width, a ring of six cameras' common one.  Such a
+        // camera sees heights `step` apart 0.75 W step / r feature pixels
+        // apart at range r; taken where that is at most 0.45 at half the grid's larger
         // extent, and where the call has enough wavefronts to be bound by
         // its loads and not by a wavefront's latency.  Measured on MI355X,
         // culled / merged us: 2 x 512 x 512 cells, 8 cameras, C = 64
@@ -2358,7 +2359,12 @@ int make_plan(const flashbev_features *f, const float *l2i, const flashbev_bev_g
         // heights have little to merge (202 x 306, 10 heights, 0.26 28.3 /
         // 28.7), and rows of at most 12 bytes little to load: they want twice
         // the wavefronts (C = 3 float32, 2581 of them 17.1 / 21.9; 2 half,
-        // 3570 26.7 / 31.9; 4 half, 4776 49.0 / 39.2).
+        // 3570 26.7 / 31.9; 4 half, 4776 49.0 / 39.2).  Other lenses than the
+        // assumed one, by focal length in image widths: the 512 x 512 cells
+        // with spacing 0.26, 0.4 711 / 513, 1.5 285 / 262, 3 182 / 193; C = 80
+        // float32 with spacing 0.33, 0.4 99 / 51, 1.5 40.6 / 36.8, 3 25.3 /
+        // 25.7.  One wide gap among dense heights raises the mean spacing and
+        // goes without.
         double step = 0.0;
         for (int k = 1; k < zb->Z; ++k) step += fabs((double)zb->z[k] - (double)zb->z[k - 1]);
         const double ex = fabs((double)s->dx) * s->X, ey = fabs((double)s->dy) * s->Y;

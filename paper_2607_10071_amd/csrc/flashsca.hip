@@ -1057,7 +1057,7 @@ sca_bwd_left(const ScaParams p)
 //   * sca_bin_alloc: gives every bin its range of the record array.
 //   * sca_bwd_points: the offset and logit gradients, and a 16-byte record
 //     (query, base, fractions, mean * a_j) of every point to each bin its
-//     footprint touches (1.2 on average).
+//     footprint touches ((1 + 1/7)^2 = 1.3 of them on average inside a map).
 //   * sca_bin_sum: sums each bin's records into its pixels in LDS and writes
 //     them, zeros included.
 //   * sca_bwd_left: adds the tiles that could not be binned (usually none).
@@ -1449,8 +1449,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // however the points crowd.  A base row's sums go to the bin's pixels in LDS
 // when the next row begins; they are this wavefront's own, so there are no
 // atomics and no barriers.  (ds_add_f32 retires 0.33 lanes per clock and CU on
-// this chip.)  Measured at BEVFormer-base, P = 8: 385 us for 13 M records,
-// matrix units busy for 90 us of it, vector issue for about 150; the same sums
+// this chip.)  Measured at BEVFormer-base, P = 8: 374 us for 12.9 M records,
+// matrix units busy for 88 us of it, vector issue for about 180; the same sums
 // by groups of lanes, one base each, took 525 us, most lanes waiting for the
 // fullest base.
 template <int SW>
@@ -2274,7 +2274,7 @@ int plan_binned(const flashsca_value *v, ScaPlan *pl, ScaWork *w)
     if (nb > (1ull << 26) || pts > (1ull << 28) || w->tiles > (1ull << 22))
         return FLASHBEV_ERR_UNSUPPORTED;
     // Records: a point has one per hit camera and bin its footprint touches,
-    // about 1.2 on a ring of six cameras, 1.6 on one of eight and so on in
+    // about 1.3 on a ring of six cameras, 1.6 on one of eight and so on in
     // proportion; a call with more (2 a point up to eight cameras) takes the
     // scatter form on the device.
     w->rec_cap = pts * (uint64_t)(p.N > 8 ? p.N : 8) / 4;
