@@ -181,14 +181,16 @@ def _packed_call(name: str, args):
     """The C entry point ``name`` with every pointer taken as an address or as
     bytes (``args``: P for pointers, i for int32, Q for uint64).  The library
     that is loaded keeps it."""
+    try:
+        return _LIB._packed_calls[name]
+    except (AttributeError, KeyError):   # not loaded yet, or not called before
+        pass
+    kinds = {"P": ctypes.c_void_p, "i": ctypes.c_int32, "Q": ctypes.c_uint64}
     lib = _lib()
-    fn = lib._packed_calls.get(name)
-    if fn is None:
-        kinds = {"P": ctypes.c_void_p, "i": ctypes.c_int32, "Q": ctypes.c_uint64}
-        fn = lib[name]
-        fn.argtypes = [kinds[k] for k in args]
-        fn.restype = ctypes.c_int
-        lib._packed_calls[name] = fn
+    fn = lib[name]
+    fn.argtypes = [kinds[k] for k in args]
+    fn.restype = ctypes.c_int
+    lib._packed_calls[name] = fn
     return fn
 
 
