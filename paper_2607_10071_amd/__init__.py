@@ -425,7 +425,9 @@ def _workspace(size: int, device, s: int):
 
     if s == torch._C._cuda_getCurrentRawStream(device.index):
         return torch.empty(size, dtype=torch.uint8, device=device)
-    with torch.cuda.stream(torch.cuda.ExternalStream(s, device=device)):
+    # (ExternalStream(0) would be a stream of torch's own)
+    stream = torch.cuda.ExternalStream(s, device=device) if s else torch.cuda.default_stream(device)
+    with torch.cuda.stream(stream):
         return torch.empty(size, dtype=torch.uint8, device=device)
 
 

@@ -204,3 +204,37 @@ def test_a_workspace_belongs_to_the_stream_of_its_call(fb, device, op, monkeypat
     assert seen[0] not in [t.data_ptr() for t in after]
     s.synchronize()
     c.check(r, op)
+
+
+@pytest.mark.parametrize("op", ["vt", "sca"])
+def test_a_workspace_on_the_default_stream_by_its_address(fb, device, op):
+    """stream=0 (the default stream's address) from within another stream: the
+    workspace comes from the default stream's pool, which is given it again."""
+    import torch
+    c = SCA(fb, device) if op == "sca" else VT(fb, device)
+    size = c.need if op == "sca" else c.best
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    block = torch.empty(size, dtype=torch.uint8, device=device)
+    mine = block.data_ptr()
+    del block   # in the default stream's pool, next in line for this size
+    seen = []
+    kept = fb._workspace
+
+    def workspace(*a):
+        t = kept(*a)
+        seen.append(t.data_ptr())
+        return t
+
+    side = torch.cuda.Stream(device)
+    side.wait_stream(torch.cuda.current_stream(device))
+    fb._workspace = workspace
+    try:
+        with torch.cuda.stream(side):
+            r = fb.sca_backward(*c.args, stream=0) if op == "sca" else \
+                fb.sample_vt_backward(*c.args, stream=0)
+    finally:
+        fb._workspace = kept
+    assert seen == [mine]
+    torch.cuda.synchronize()
+    c.check(r, f"{op}, stream 0")
